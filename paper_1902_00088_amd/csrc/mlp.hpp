@@ -18,9 +18,7 @@ struct MlpArgs {
   const float* mean;  // [nf] normalisation
   const float* std;
   float* xn;          // [n][nin] normalised features (saved for the gradient)
-  float* z1;          // [n][64]
-  float* a1;
-  float* z2;
+  float* a1;          // [n][64]
   float* a2;
   float* logits;      // [n][3]
   const int8_t* y;    // [n] labels
@@ -34,19 +32,17 @@ struct MlpArgs {
 };
 
 struct MlpAdamArgs {
-  float* p;
-  const float* g;
+  float* p;           // null: gradients only
   float* m;
   float* v;
-  int n;
   float lr, b1, b2, eps, bc1, bc2;
 };
 
 int mlp_param_count(int nin);
 hipError_t launch_pool(int bs, int grid, const MlpPoolArgs& a, hipStream_t st);
 hipError_t launch_mlp_forward(const MlpArgs& a, hipStream_t st);
-hipError_t launch_mlp_backward(const MlpArgs& a, hipStream_t st);  // loss, deltas, parameter gradients
-hipError_t launch_adam(const MlpAdamArgs& a, hipStream_t st);
+// forward pass, loss, deltas, parameter gradients and (adam.p set) their Adam update
+hipError_t launch_mlp_train(const MlpArgs& a, const MlpAdamArgs& adam, hipStream_t st);
 hipError_t launch_pred(const float* logits, int n, int8_t* pred, float* pmax, hipStream_t st);
 
 }  // namespace mrb

@@ -311,7 +311,7 @@ struct mrb_ctx {
   // learned predictor: model, Adam state and batch workspace (device)
   int mlp_nin = 0, mlp_np = 0, mlp_t = 0, mlp_cap = 0;
   float *mp = nullptr, *mgrad = nullptr, *mm = nullptr, *mv = nullptr, *mnorm = nullptr;
-  float *mx = nullptr, *mxn = nullptr, *mz1 = nullptr, *ma1 = nullptr, *mz2 = nullptr, *ma2 = nullptr;
+  float *mx = nullptr, *mxn = nullptr, *ma1 = nullptr, *ma2 = nullptr;
   float *mlog = nullptr, *mloss = nullptr, *mdl = nullptr, *mdz1 = nullptr, *mdz2 = nullptr, *mcw = nullptr;
   float* mpmax = nullptr;
   int8_t *my = nullptr, *mpred = nullptr;
@@ -2542,7 +2542,7 @@ mrb_status mrb_destroy(mrb_ctx* c) {
   for (auto& t : c->timed) { (void)hipEventDestroy(t.a); (void)hipEventDestroy(t.b); }
   for (auto& g : c->graphs) (void)hipGraphExecDestroy(g.exec);
   for (auto e : c->ev_pool) (void)hipEventDestroy(e);
-  void* mlpbufs[] = {c->mp, c->mgrad, c->mm, c->mv, c->mnorm, c->mx, c->mxn, c->mz1, c->ma1, c->mz2, c->ma2,
+  void* mlpbufs[] = {c->mp, c->mgrad, c->mm, c->mv, c->mnorm, c->mx, c->mxn, c->ma1, c->ma2,
                      c->mlog, c->mloss, c->mdl, c->mdz1, c->mdz2, c->mcw, c->mpmax, c->my, c->mpred};
   for (void* p : mlpbufs)
     if (p) (void)hipFree(p);
@@ -3371,8 +3371,7 @@ mrb_status mlp_ready(mrb_ctx* c) {
 mrb_status mlp_workspace(mrb_ctx* c, int n) {
   if (n <= c->mlp_cap) return MRB_OK;
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  float** fl[] = {&c->mx, &c->mxn, &c->mz1, &c->ma1, &c->mz2, &c->ma2, &c->mlog, &c->mloss, &c->mdl, &c->mdz1,
-                  &c->mdz2, &c->mpmax};
+  float** fl[] = {&c->mx, &c->mxn, &c->ma1, &c->ma2, &c->mlog, &c->mloss, &c->mdl, &c->mdz1, &c->mdz2, &c->mpmax};
   for (float** p : fl)
     if (*p) { (void)hipFree(*p); *p = nullptr; }
   if (c->my) { (void)hipFree(c->my); c->my = nullptr; }
@@ -3380,9 +3379,7 @@ mrb_status mlp_workspace(mrb_ctx* c, int n) {
   const size_t N = (size_t)n;
   HIPCHK(c, hipMalloc(&c->mx, N * c->mlp_nin * 4));
   HIPCHK(c, hipMalloc(&c->mxn, N * c->mlp_nin * 4));
-  HIPCHK(c, hipMalloc(&c->mz1, N * 64 * 4));
   HIPCHK(c, hipMalloc(&c->ma1, N * 64 * 4));
-  HIPCHK(c, hipMalloc(&c->mz2, N * 64 * 4));
   HIPCHK(c, hipMalloc(&c->ma2, N * 64 * 4));
   HIPCHK(c, hipMalloc(&c->mlog, N * 3 * 4));
   HIPCHK(c, hipMalloc(&c->mloss, N * 4));
@@ -3407,9 +3404,7 @@ MlpArgs mlp_args(mrb_ctx* c, int off, int n) {
   a.mean = c->mnorm;
   a.std = c->mnorm + 4;
   a.xn = c->mxn + o * c->mlp_nin;
-  a.z1 = c->mz1 + o * 64;
   a.a1 = c->ma1 + o * 64;
-  a.z2 = c->mz2 + o * 64;
   a.a2 = c->ma2 + o * 64;
   a.logits = c->mlog + o * 3;
   a.y = c->my + o;
@@ -3525,8 +3520,7 @@ mrb_status mrb_mlp_grad(mrb_ctx* c, const float* x, const int8_t* y, const float
   HIPCHK(c, hipMemcpyAsync(c->mcw, classw, 3 * 4, hipMemcpyHostToDevice, c->stream));
   MlpArgs a = mlp_args(c, 0, n);
   a.inv_wsum = (float)batch_inv_wsum(y, n, classw);
-  HIPCHK(c, launch_mlp_forward(a, c->stream));
-  HIPCHK(c, launch_mlp_backward(a, c->stream));
+  HIPCHK(c, launch_mlp_train(a, MlpAdamArgs{}, c->stream));
   std::vector<float> ls(n);
   if (grads) HIPCHK(c, hipMemcpyAsync(grads, c->mgrad, (size_t)c->mlp_np * 4, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipMemcpyAsync(ls.data(), c->mloss, (size_t)n * 4, hipMemcpyDeviceToHost, c->stream));
@@ -3547,7 +3541,6 @@ mrb_status mrb_mlp_train(mrb_ctx* c, const float* x, const int8_t* y, const floa
     if (y[i] < 0 || y[i] > 2) return fail(c, MRB_E_ARG, "mlp: labels must be 0, 1 or 2");
   mrb_status r = mlp_workspace(c, n);
   if (r) return r;
-  HIPCHK(c, hipMemcpyAsync(c->mx, x, (size_t)n * c->mlp_nin * 4, hipMemcpyHostToDevice, c->stream));
   HIPCHK(c, hipMemcpyAsync(c->my, y, (size_t)n, hipMemcpyHostToDevice, c->stream));
   HIPCHK(c, hipMemcpyAsync(c->mcw, classw, 3 * 4, hipMemcpyHostToDevice, c->stream));
   const double b1 = 0.9, b2 = 0.999;
@@ -3556,12 +3549,13 @@ mrb_status mrb_mlp_train(mrb_ctx* c, const float* x, const int8_t* y, const floa
     const int m = std::min(batch, n - off);
     MlpArgs a = mlp_args(c, off, m);
     a.inv_wsum = (float)batch_inv_wsum(y + off, m, classw);
-    HIPCHK(c, launch_mlp_forward(a, c->stream));
-    HIPCHK(c, launch_mlp_backward(a, c->stream));
+    // each batch's rows just before its launches: the host stages the next ones meanwhile
+    HIPCHK(c, hipMemcpyAsync(c->mx + (size_t)off * c->mlp_nin, x + (size_t)off * c->mlp_nin,
+                             (size_t)m * c->mlp_nin * 4, hipMemcpyHostToDevice, c->stream));
     c->mlp_t++;
-    MlpAdamArgs ad{c->mp, c->mgrad, c->mm, c->mv, c->mlp_np, lr, (float)b1, (float)b2, 1e-8f,
+    MlpAdamArgs ad{c->mp, c->mm, c->mv, lr, (float)b1, (float)b2, 1e-8f,
                    (float)(1.0 - std::pow(b1, c->mlp_t)), (float)(1.0 - std::pow(b2, c->mlp_t))};
-    HIPCHK(c, launch_adam(ad, c->stream));
+    HIPCHK(c, launch_mlp_train(a, ad, c->stream));
   }
   std::vector<float> ls(n);
   HIPCHK(c, hipMemcpyAsync(ls.data(), c->mloss, (size_t)n * 4, hipMemcpyDeviceToHost, c->stream));

@@ -120,6 +120,30 @@ def test_forward_loss_and_gradient_vs_oracle(nf, n):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("nf", [1, 4])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 64, 65, 1023, 1025])
+def test_predictor_tile_edges(nf, n):
+    """Sample counts around the kernels' tiles (16 samples a workgroup, 64 a wave's share of the
+    gradient's batch split).  FP32 sums of up to 64 nf + 64 + 64 terms: relative error at most
+    about terms x 2^-24 of the sum of magnitudes, 2e-5, and a factor 5 for the activations."""
+    cfg = W.C3(jmax=2) if nf == 4 else W.C1(jmax=2)
+    s = M.Solver(cfg)
+    nin, p, mean, std = _model(nf, seed=11)
+    s.mlp_init(p, mean, std)
+    x, y = _inputs(n, nin, 100 + n)
+    cw = W.class_weights(y).astype(np.float32)
+    xn = OM.normalise(x.astype(np.float64), mean.astype(np.float64), std.astype(np.float64), nf)
+    z3, _ = OM.forward(p.astype(np.float64), xn, nin)
+    got = s.mlp_forward(x)
+    assert np.abs(got - z3).max() <= 1e-4 * max(1.0, float(np.abs(z3).max()))
+    loss, g = s.mlp_grad(x, y, cw)
+    lref, gref = OM.loss_and_grad(p.astype(np.float64), xn, y, cw.astype(np.float64), nin)
+    assert abs(loss - lref) <= 1e-4 * max(1.0, abs(lref))
+    assert np.abs(g - gref).max() <= 1e-4 * float(np.abs(gref).max())
+    s.close()
+
+
+@pytest.mark.gpu
 def test_adam_epoch_vs_oracle():
     """Three ragged batches (1024, 1024, 452), one Adam step each."""
     cfg = W.C3(jmax=3)
