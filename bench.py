@@ -35,10 +35,14 @@ def counter_traffic(key):
     if key is None:
         return None
     path = os.path.join(ROOT, "profiles", "stage_traffic_counters.md")
-    src = os.path.join(ROOT, "paper_1902_00088_amd", "csrc", "kernels.hip")
+    csrc = os.path.join(ROOT, "paper_1902_00088_amd", "csrc")
     try:
         text = open(path).read()
-        sha = hashlib.sha256(open(src, "rb").read()).hexdigest()
+        src = open(os.path.join(csrc, "kernels.hip"), "rb").read()
+        for name in ("column3.hip", "device.hpp"):   # the kernels' other sources
+            if os.path.exists(os.path.join(csrc, name)):
+                src += open(os.path.join(csrc, name), "rb").read()
+        sha = hashlib.sha256(src).hexdigest()
     except OSError:
         return None
     vals = {}

@@ -210,6 +210,12 @@ hipError_t launch_stage(const Shape& s, int precision, Variant v, int grid, cons
 // variant is not compiled.
 hipError_t launch_sweep(const Shape& s, int precision, Variant v, int max_grid, const SweepArgs& a, hipStream_t st,
                         int* grid_out);
+// whole 3D blocks, a column along z per thread (column3.hip): the stage variant of
+// kColumnThreads threads, the analysis and the refinement
+constexpr int kColumnThreads = 448;
+hipError_t launch_stage3(int precision, const StageArgs& a, hipStream_t st);
+hipError_t launch_mr3(const MrArgs& a, hipStream_t st);
+hipError_t launch_refine3(const RefineArgs& a, hipStream_t st);
 hipError_t launch_plain(const Shape& s, int grid, const StageArgs& a, hipStream_t st);  // ghost + RHS kernels
 // overlapped-tile RK4 step; hipErrorInvalidValue if the shape has no such kernel
 // (threads per workgroup: 256; with the analysis on whole blocks also 512 or 1024;

@@ -1085,3 +1085,48 @@ def test_device_topology_capacity_error_leaves_state():
     assert np.array_equal(s.read_forest()[0], lvb) and np.array_equal(s.read_forest()[1], cob)
     assert np.array_equal(_bits(s.read_blocks()), _bits(before))
     s.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("seed,p_refine,jmin", [(0, 0.45, 1), (1, 0.3, 1), (5, 0.7, 1), (2, 0.1, 2)])
+def test_3d_column_kernels_on_ragged_forests(seed, p_refine, jmin):
+    """The default 3D stage, analysis and refinement (a column per thread, owners per zone) on
+    random graded forests with every kind of neighbour: FP64 bitwise against the oracle, mixed
+    bitwise against the sub-tiled kernels (the same operations per point)."""
+    cfg = W.C4(jmax=4, eps=1e-2, max_blocks=9000)
+    lv, co = W.random_graded_forest(3, 3, seed, p_refine, jmin)
+    s, o = M.Solver(cfg), oracle.Oracle(cfg)
+    o.init_forest(lv, co)
+    lv, co = o.read_forest()
+    data = W.sample(cfg, lv, co)
+    data = data + 1e-3 * np.cos(37.0 * data)          # details of every size
+    s.init_forest(lv, co)
+    s.load_blocks(data)
+    o.load_blocks(data)
+    assert s.stats()["stage_threads"] == 448
+    for k in range(2):
+        s.rk4(k * cfg.dt, cfg.dt)
+        o.rk4(k * cfg.dt, cfg.dt)
+    assert np.array_equal(s.read_blocks(), o.read_blocks())
+    f1, m1 = s.mr_pass()
+    f2, m2 = o.mr_pass()
+    assert np.array_equal(f1, f2) and np.array_equal(m1, m2)
+    assert np.array_equal(s.read_blocks(), o.read_blocks())      # the written-back nodes
+    s.refine_all()
+    o.refine_all()
+    assert np.array_equal(s.read_blocks(), o.read_blocks())
+    assert s.adapt() == o.adapt()
+    assert np.array_equal(s.read_blocks(), o.read_blocks())
+    s.close()
+    mixed = []
+    for force in (0, 2):
+        s = M.Solver(cfg.replace(precision=W.MIXED))
+        s.init_forest(lv, co)
+        s.load_blocks(data)
+        if force:
+            s.tune(nsub=force)
+        for k in range(2):
+            s.rk4(k * cfg.dt, cfg.dt)
+        mixed.append(s.read_blocks())
+        s.close()
+    assert np.array_equal(mixed[0], mixed[1])
