@@ -178,7 +178,12 @@ struct CoarsenArgs {
   double* u;
 };
 
-// shock-capturing filter of the Navier-Stokes shape: reads u, writes unew
+// Shock-capturing filter of the Navier-Stokes shape, after a time step: per axis a pressure
+// sensor s = max(0, 1 - r_th / r) with r = M / p^2 + 1e-16,
+// M = ((Dp_j - Dp_{j+1})^2 + (Dp_j - Dp_{j-1})^2) / 2, Dp_j = (-p_{j+1} + 2 p_j - p_{j-1}) / 4,
+// switches a second-order filter in flux form on every field:
+// q_i - [(s_{i+1/2} F_{i+1/2} - s_{i-1/2} F_{i-1/2})_x + (...)_y], s_{i+1/2} = (s_i + s_{i+1}) / 2,
+// F_{i+1/2} = -(q_{i+1} - q_i) / 4, on the synchronised state; reads u, writes unew
 struct FilterArgs {
   Topo topo;
   const double* u;
@@ -216,6 +221,15 @@ constexpr int kColumnThreads = 448;
 hipError_t launch_stage3(int precision, const StageArgs& a, hipStream_t st);
 hipError_t launch_mr3(const MrArgs& a, hipStream_t st);
 hipError_t launch_refine3(const RefineArgs& a, hipStream_t st);
+// 2D stages of whole blocks (halves of them for Navier-Stokes) and the filter (plane2.hip):
+// the stage variant of plane_threads threads
+constexpr int kNsThreads = 576;
+hipError_t launch_stage2(const Shape& s, int precision, const StageArgs& a, hipStream_t st);
+hipError_t launch_filter(const FilterArgs& a, hipStream_t st);   // NS shape only
+// threads of the zone-owner stage kernel of a shape (column3.hip, plane2.hip)
+inline int zone_threads(const Shape& s) {
+  return s.dim == 3 ? kColumnThreads : (s.nf == 4 ? kNsThreads : (s.bs == 33 ? 576 : 448));
+}
 hipError_t launch_plain(const Shape& s, int grid, const StageArgs& a, hipStream_t st);  // ghost + RHS kernels
 // overlapped-tile RK4 step; hipErrorInvalidValue if the shape has no such kernel
 // (threads per workgroup: 256; with the analysis on whole blocks also 512 or 1024;
@@ -230,7 +244,6 @@ int mr_threads(const Shape& s, int nsub, int* tpb, int cap);   // compiled workg
 hipError_t launch_refine(const Shape& s, int nsub, int grid, const RefineArgs& a, hipStream_t st);
 hipError_t launch_coarsen(const Shape& s, int grid, const CoarsenArgs& a, hipStream_t st);
 hipError_t launch_read(const Shape& s, int grid, const ReadArgs& a, hipStream_t st);
-hipError_t launch_filter(const Shape& s, int grid, const FilterArgs& a, hipStream_t st);   // NS shape only
 hipError_t launch_scatter(const double* src, const int* slots, int n, size_t bsz, double* dst, hipStream_t st);
 // Device-resident topology transitions (topo.hip).  Arenas share the TopoHeader layout;
 // old_* is the current grid, new_* the next one.

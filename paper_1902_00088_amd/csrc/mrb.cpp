@@ -886,14 +886,18 @@ int pick_nsub(const mrb_ctx* c) {
 // threads per workgroup of the stage kernel: the tuned choice for the tuned tiling
 int pick_tpb(const mrb_ctx* c, int nsub) { return c->nsub == nsub ? c->tpb : 256; }
 
-// The stage kernel and its tiling: the forced or tuned one, else in 3D whole blocks with a
-// column per thread, else by block count (pick_nsub).  In 3D the column kernel is the
-// faster one at every size: an RK4 step of 8 blocks takes 42 us in FP64 and 36 us mixed
-// against 44 and 41 us in 2 x 2 x 2 sub-tiles, 512 blocks 93 and 68 us against 238 and 222.
+// The stage kernel and its tiling: the forced or tuned one, else whole blocks (halves in
+// Navier-Stokes) with the owners resolved per zone (column3.hip, plane2.hip).  Against the
+// best tiling of the point-owner kernels, an RK4 step takes: 512 3D blocks 93 us against 238
+// (FP64), 68 against 107 (mixed), 8 blocks 42 against 44; 1,024 blocks of 33^2 53 against 73,
+// 64 blocks 22 against 24; 1,024 Navier-Stokes blocks 158 against 267; 1,024 blocks of 17^2
+// 28 against 28, 4 to 256 blocks 16-20 against 19-23.  Only where 4 x 4 sub-tiles of 33^2
+// blocks still leave compute units idle do those win: 16 blocks 20.7 against 22.0 us,
+// Navier-Stokes 28.1 against 31.2.
 Variant pick_stage(const mrb_ctx* c) {
-  const Variant column{1, kColumnThreads};
-  if (c->shape.dim == 3 && c->nsub == 1 && c->tpb == kColumnThreads) return column;
-  if (c->shape.dim == 3 && c->nsub == 0) return column;
+  const Variant zoned{1, zone_threads(c->shape)};
+  const bool tiny = c->shape.dim == 2 && c->shape.bs == 33 && 16 * (long)nblk(c) <= c->ncu;
+  if ((c->nsub == 0 && !tiny) || (c->nsub == 1 && c->tpb == zoned.tpb)) return zoned;
   const int nsub = pick_nsub(c);
   return Variant{nsub, pick_tpb(c, nsub)};
 }
@@ -1107,7 +1111,7 @@ mrb_status do_filter(mrb_ctx* c) {
   FilterArgs a{topo(c), c->u, c->unew, c->cfg.phys[3]};
   {
     TimeScope ts(c, T_FILTER, (double)n * c->bsz * 16.0);
-    HIPCHK(c, launch_filter(c->shape, grid_for(c, n), a, c->stream));
+    HIPCHK(c, launch_filter(a, c->stream));
   }
   std::swap(c->u, c->unew);
   return MRB_OK;
@@ -2999,8 +3003,8 @@ mrb_status mrb_tune(mrb_ctx* c, int nsub, int reps, double dt, int* chosen) {
       for (int j = 0; j < nt; ++j)
         for (int o = 0; o < 2; ++o) cand.push_back(Cand{v[i], tv[j], o, 1e30f});
     }
-    if (c->shape.dim == 3 && std::find(v, v + nv, 1) == v + nv)   // whole 3D blocks in FP64: columns only
-      for (int o = 0; o < 2; ++o) cand.push_back(Cand{1, kColumnThreads, o, 1e30f});
+    if (std::find(v, v + nv, 1) == v + nv)   // whole blocks as the zone-owner kernel only
+      for (int o = 0; o < 2; ++o) cand.push_back(Cand{1, zone_threads(c->shape), o, 1e30f});
     for (int round = 0; round < kRounds; ++round)
       for (Cand& k : cand) {
         c->nsub = k.nsub;

@@ -1,0 +1,571 @@
+// 2D stage and filter kernels over whole blocks or halves of blocks (gfx950): advection on
+// blocks of 33^2 or 17^2 points, Navier-Stokes (four fields, halo 4) on 33^2.
+//
+// As in column3.hip, the owner of a tile point (the finest leaf holding it on its own
+// lattice, Sec. 2.2 and Sec. 2.5) only depends on its zone along each axis -- before the
+// block, its first node, the first half, the middle node, the second half, its last node,
+// beyond -- so a workgroup resolves the owners of 7^2 zones once, and a thread forms the
+// addresses of its few tile points with one look-up each and has all their loads (every
+// field) in flight together.
+#include "device.hpp"
+
+#include <hip/hip_runtime.h>
+#include <algorithm>
+
+namespace mrb {
+
+namespace {
+
+constexpr int NZ = 7;   // zones per axis
+
+template <int BS>
+__device__ __forceinline__ constexpr int zone_of(int t) {
+  constexpr int M = (BS - 1) / 2;
+  return t < 0 ? 0 : (t == 0 ? 1 : (t < M ? 2 : (t == M ? 3 : (t < 2 * M ? 4 : (t == 2 * M ? 5 : 6)))));
+}
+
+// Tile of a block's rows [y0, y0 + SY) (all columns) with a halo of HW, and the coarse
+// lattice (even points up to HW + 3 beyond) that predictions read
+template <int BS, int NF, int HW, int SY, int TPB>
+struct Tile2 {
+  static constexpr int NP = BS * BS, TW = BS + 2 * HW, TH = SY + 2 * HW, TSZ = TW * TH, H = HW + 3;
+  static constexpr int RG = TPB / TW, NR = (TH + RG - 1) / RG;   // row groups, rows per thread
+  static constexpr int ROWS = SY + 2 * H;   // rows of the owner table
+  static constexpr int CW = (BS + 2 * H + 1) / 2, CH = (SY + 2 * H + 1) / 2, CSZ = CW * CH;
+  static_assert(RG >= 1, "a tile row fits the workgroup");
+  __device__ static __forceinline__ int first_even(int r0) { return (r0 - H + 1) & ~1; }
+};
+
+// Owner of the points of a row and a zone along x, the row folded into its base: rows
+// y0 - H .. y0 + SY - 1 + H of a tile.  A coarser owner (sh 2) holds even points only.
+template <int ROWS>
+struct Rows2 {
+  unsigned long long m[2][NZ];   // entries whose box holds the zone, per axis
+  SEnt se[64];
+  SEnt tab[ROWS * NZ];           // x zone fastest
+};
+
+// owners of the tile's rows (see zone_table in column3.hip)
+template <int BS, int NF, int TPB, int ROWS>
+__device__ __forceinline__ void row_table(Rows2<ROWS>& z, const BlockDesc& d, const NbEntry* ent, int stride, int first) {
+  constexpr int M = (BS - 1) / 2, NP = BS * BS;
+  const int lane = threadIdx.x & 63;
+  NbEntry E{};
+  if (lane < stride) E = ent[lane];
+  const bool live = lane < d.n_ent;
+  const int ext = E.dl > 0 ? M : (E.dl == 0 ? BS - 1 : 2 * (BS - 1));
+  for (int q = threadIdx.x >> 6; q < 2 * NZ; q += TPB / 64) {
+    const int a = q / NZ, k = q % NZ;
+    const int t = k == 0 ? -1 : (k == 1 ? 0 : (k == 2 ? 1 : (k == 3 ? M : (k == 4 ? M + 1 : (k == 5 ? 2 * M : 2 * M + 1)))));
+    const int l = t - (a == 0 ? E.o[0] : E.o[1]);
+    const unsigned long long mm = __ballot(live && l >= 0 && l <= ext);
+    if (lane == 0) z.m[a][k] = mm;
+  }
+  if (threadIdx.x < 64) {
+    const int sh = 1 - E.dl;
+    z.se[lane] = SEnt{E.slot * NF * NP - (((2 * E.o[0]) >> sh) + BS * ((2 * E.o[1]) >> sh)), sh};
+  }
+  __syncthreads();
+  for (int p = threadIdx.x; p < ROWS * NZ; p += TPB) {
+    const int ty = first + p / NZ;
+    const unsigned long long c = z.m[0][p % NZ] & z.m[1][zone_of<BS>(ty)];
+    const SEnt e = z.se[c ? 63 - __clzll((long long)c) : 0];
+    z.tab[p] = SEnt{e.base + BS * ((2 * ty) >> e.sh), e.sh};
+  }
+  __syncthreads();
+}
+
+// This thread's tile points (column x, rows rg + i RG): values of every field, owned or
+// predicted, in registers.  carr: LDS of 2 NF CSZ values (the coarse lattice and its odd
+// points along x), used by blocks with coarser neighbours only.  load(address, field's offset)
+// fetches a stored point, val(fetched, field) turns it into the tile's value.
+template <int BS, int NF, int HW, int SY, int TPB, typename TT>
+struct Gather2 {
+  using T2 = Tile2<BS, NF, HW, SY, TPB>;
+  TT v[T2::NR][NF];
+  int x, rg;
+  unsigned in;   // bit i: row i lies in the tile
+
+  template <typename Z, typename LOAD, typename VAL>
+  __device__ __forceinline__ void run(TT* carr, const Z& zn, int self, bool hasc, int y0, int cnty, const LOAD& load,
+                                      const VAL& val) {
+    constexpr int NR = T2::NR, TW = T2::TW, RG = T2::RG, CW = T2::CW, CSZ = T2::CSZ, NP = T2::NP, H = T2::H;
+    using R = typename LOAD::type;   // what a load returns (u, and the slope where there is one)
+    const int tid = threadIdx.x;
+    x = tid % TW;
+    rg = tid / TW;
+    const int tx = x - HW, zx = zone_of<BS>(tx), cx0 = T2::first_even(0), cy0 = T2::first_even(y0);
+    unsigned held = 0;
+    in = 0;
+    int ad[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const int r = rg + RG * i, ty = y0 - HW + r;
+      const SEnt E = zn.tab[zx + NZ * min(r + 3, T2::ROWS - 1)];
+      const bool ok = rg < RG && r < cnty + 2 * HW, h = E.sh < 2 || ((tx | ty) & 1) == 0;
+      if (ok) in |= 1u << i;
+      if (h) held |= 1u << i;
+      // (points nobody holds, and rows past the tile, load the block's first node)
+      ad[i] = ok && h ? E.base + ((2 * tx) >> E.sh) : self;
+    }
+    R raw[NR][NF];
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+#pragma unroll
+      for (int f = 0; f < NF; ++f) raw[i][f] = load(ad[i], f * NP);
+    if (hasc) {
+      // coarse-lattice points outside the tile
+      for (int p = tid; p < CSZ; p += TPB) {
+        const int sx = cx0 + 2 * (p % CW), sy = cy0 + 2 * (p / CW);
+        const bool inside = sx >= -HW && sx < BS + HW && sy >= y0 - HW && sy < y0 + cnty + HW;
+        if (inside || sx > BS - 1 + H || sy > y0 + cnty - 1 + H || sy < y0 - H) continue;
+        const SEnt E = zn.tab[zone_of<BS>(sx) + NZ * (sy - y0 + H)];
+        const int a = E.base + ((2 * sx) >> E.sh);
+        R q[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) q[f] = load(a, f * NP);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) carr[f * CSZ + p] = val(q[f], f);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+#pragma unroll
+      for (int f = 0; f < NF; ++f) v[i][f] = val(raw[i][f], f);
+    if (!hasc) return;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const int ty = y0 - HW + rg + RG * i;
+      if (((in >> i) & 1u) && ((tx | ty) & 1) == 0) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) carr[f * CSZ + (tx - cx0) / 2 + CW * ((ty - cy0) / 2)] = v[i][f];
+      }
+    }
+    __syncthreads();
+    // the points between two coarse ones along x (entry i: between coarse points i + 1, i + 2)
+    TT* codd = carr + NF * CSZ;
+    for (int p = tid; p < NF * CSZ; p += TPB) {
+      if (p % CW >= CW - 3) continue;
+      codd[p] = P4(carr[p], carr[p + 1], carr[p + 2], carr[p + 3]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const int ty = y0 - HW + rg + RG * i;
+      if (((held >> i) & 1u) || !((in >> i) & 1u)) continue;
+      const int dx = tx - cx0, dy = ty - cy0;
+      const TT* c = ((tx & 1) ? codd + (dx - 3) / 2 : carr + dx / 2) + CW * ((ty & 1) ? (dy - 3) / 2 : dy / 2);
+#pragma unroll
+      for (int f = 0; f < NF; ++f) {
+        const TT* q = c + f * CSZ;
+        v[i][f] = (ty & 1) ? P4(q[0], q[CW], q[2 * CW], q[3 * CW]) : q[0];
+      }
+    }
+  }
+};
+
+// sources: u alone, or u and the previous slope
+struct LoadU {
+  using type = double;
+  const double* u;
+  __device__ __forceinline__ type operator()(int i, int o) const { return (u + o)[(unsigned)i]; }
+};
+template <typename KT>
+struct UK {
+  double u;
+  KT k;
+};
+template <typename KT>
+struct LoadUK {
+  using type = UK<KT>;
+  const double* u;
+  const KT* k;
+  __device__ __forceinline__ type operator()(int i, int o) const { return type{(u + o)[(unsigned)i], (k + o)[(unsigned)i]}; }
+};
+
+// stage value from what was loaded, minus the field offset in FP32 tiles
+template <typename TT>
+struct StageValue {
+  double alpha;
+  const double* off;
+  __device__ __forceinline__ TT fin(double y, int f) const {
+    if constexpr (sizeof(TT) == 4) return (TT)(y - off[f]);
+    else return y;
+  }
+  __device__ __forceinline__ TT operator()(double u, int f) const { return fin(u, f); }
+  template <typename KT>
+  __device__ __forceinline__ TT operator()(const UK<KT>& q, int f) const { return fin(q.u + alpha * (double)q.k, f); }
+};
+
+template <typename KT, typename F>
+__device__ __forceinline__ void with_source(const StageArgs& A, const F& f) {
+  if (A.stage == 1) f(LoadU{A.u});
+  else f(LoadUK<KT>{A.u, (const KT*)A.kprev});
+}
+
+// ---------------------------------------------------------------------------
+// Advection stage (constant velocity or swirl) of a whole block per workgroup, one (17^2) or
+// two to three (33^2) tile points per thread.  Latency bound: the descriptor and entry row,
+// the owner table, one round of loads, LDS, the update.  1,400 blocks of 33^2 FP64: 15.8 us a
+// stage against 22.3 us; 40 blocks of 17^2: 5.3 against 6.5 us.
+// ---------------------------------------------------------------------------
+template <int BS, int TPB, typename TT, typename KT>
+__global__ void __launch_bounds__(TPB) k_stage2(StageArgs A) {
+  constexpr int HW = 2;
+  using G = Gather2<BS, 1, HW, BS, TPB, TT>;
+  using T2 = typename G::T2;
+  constexpr int TW = T2::TW, NP = T2::NP;
+  __shared__ Rows2<T2::ROWS> zn;
+  __shared__ double sw[4 * BS];
+  __shared__ TT tile[T2::TSZ];
+  __shared__ TT carr[2 * T2::CSZ];
+  const XcdWork it(A.topo.h.n_blocks);   // one work item per workgroup
+  if (!it.ok()) return;
+  const int tid = threadIdx.x;
+  const int b = A.order ? A.topo.list()[it.w] : it.w;
+  const BlockDesc d = A.topo.blk()[b];
+  const bool swirl = A.ph.kind == 1;
+  if (swirl) {
+    // table slices at the block's nodes: s2(x), s(x), s2(y), s(y)
+    const int nl = A.lt.nl[d.level], shift = A.ph.jmax - d.level;
+    for (int q = tid; q < 4 * BS; q += TPB) {
+      const int k = q / BS, l = q % BS;
+      int gg = (k < 2 ? d.c[0] : d.c[1]) * (BS - 1) + l;
+      if (gg >= nl) gg -= nl;
+      gg <<= shift;
+      sw[q] = (k & 1) ? A.ph.s[gg] : A.ph.s2[gg];
+    }
+  }
+  row_table<BS, 1, TPB>(zn, d, A.topo.nb(b), A.topo.h.nb_stride, -T2::H);
+  const int base = d.slot * NP;
+  G g;
+  const StageValue<TT> val{A.alpha, A.off};
+  with_source<KT>(A, [&](const auto& src) { g.run(carr, zn, base, d.n_coarse > 0, 0, BS, src, val); });
+#pragma unroll
+  for (int i = 0; i < T2::NR; ++i)
+    if ((g.in >> i) & 1u) tile[g.x + TW * (g.rg + T2::RG * i)] = g.v[i][0];
+  __syncthreads();
+  TT r;
+  if constexpr (sizeof(TT) == 8) r = A.lt.r[d.level];
+  else r = A.lt.rf[d.level];
+  const int node0 = base;
+  constexpr int NU = (NP + TPB - 1) / TPB;
+  double e1[NU], e2[NU], e3[NU], eu[NU];
+  if (A.stage == 4) {
+#pragma unroll
+    for (int q = 0; q < NU; ++q) {
+      const int p = node0 + min(tid + q * TPB, NP - 1);
+      e1[q] = (double)((const KT*)A.k1)[p];
+      e2[q] = (double)((const KT*)A.k2)[p];
+      e3[q] = (double)((const KT*)A.k3)[p];
+      eu[q] = A.u[p];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < NU; ++q) {
+    const int p = tid + q * TPB;
+    if (p >= NP) continue;
+    const int ly = p / BS, lx = p - ly * BS;
+    const TT* T = tile + lx + HW + TW * (ly + HW);
+    const TT dx = D4(T[-2], T[-1], T[1], T[2], r);
+    const TT dy = D4(T[-2 * TW], T[-TW], T[TW], T[2 * TW], r);
+    TT kv;
+    if (swirl) {
+      const double U = (sw[lx] * sw[3 * BS + ly]) * A.cfac;
+      const double W = -((sw[2 * BS + ly] * sw[BS + lx]) * A.cfac);
+      kv = -(((TT)U * dx) + ((TT)W * dy));
+    } else {
+      TT acc = (TT)A.ph.c[0] * dx;
+      acc = acc + (TT)A.ph.c[1] * dy;
+      kv = -acc;
+    }
+    if (A.stage < 4) ((KT*)A.kout)[node0 + p] = (KT)kv;
+    else A.unew[node0 + p] = eu[q] + A.h6 * ((e1[q] + (double)kv) + 2.0 * (e2[q] + e3[q]));
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Navier-Stokes stage (primitive variables rho, u, v, p) of half a block per workgroup
+// (rows 0..16 or 17..32, one node per thread).  The tile is FP64, CT the arithmetic type
+// (see ns_fluxes in kernels.hip, whose operations these are, point by point).  p / rho is
+// formed once per tile point (it had cost eight FP64 divisions per flux point), and a
+// node's gradients, stresses and momentum factors pass from its fluxes to its right-hand
+// side in registers.  Bound by vector instructions (4,800 a half block, half of their
+// issue slots), LDS reads (40 of 100 us) and memory (260 MB, 50 us) together, overlapped by
+// the two workgroups that fit a compute unit's LDS; thirds of blocks (three workgroups) are
+// no faster, quarters slower.  2,944 blocks on five levels: 100 us a stage mixed against
+// 244 us for whole blocks of 256 threads; 1,024 blocks FP64: 43 against 76 us.
+// ---------------------------------------------------------------------------
+constexpr int NB = 33, NSY = 17, NST = kNsThreads, NPART = (NB + NSY - 1) / NSY;
+
+template <typename CT>
+__device__ __forceinline__ CT D4d(double um2, double um1, double up1, double up2, CT r) {
+  if constexpr (sizeof(CT) == 8) return D4(um2, um1, up1, up2, r);
+  else return (8.0f * (CT)(up1 - um1) - (CT)(up2 - um2)) * r;
+}
+
+template <typename KT, typename CT>
+struct NsLds {
+  using T2 = Tile2<NB, 4, 4, NSY, NST>;
+  static constexpr int FX = NB + 4, FY = NSY + 4;            // flux points -2 .. 34, -2 .. cnt + 1
+  static constexpr int NXX = FX * NSY, NYY = NB * FY, NXY = FX * FY;
+  static constexpr size_t tile = sizeof(double) * T2::TSZ * 5;   // four fields and p / rho
+  static constexpr size_t flux = sizeof(CT) * (2 * NXX + 2 * NYY + NXY), lat = sizeof(double) * 2 * 4 * T2::CSZ;
+  static constexpr size_t bytes = tile + (flux > lat ? flux : lat);   // (the lattice is dead before the fluxes)
+};
+
+template <typename KT, typename CT>
+__global__ void __launch_bounds__(NST) k_stage_ns(StageArgs A) {
+  using L = NsLds<KT, CT>;
+  using G = Gather2<NB, 4, 4, NSY, NST, double>;
+  using T2 = typename G::T2;
+  constexpr int TW = T2::TW, TSZ = T2::TSZ, NP = T2::NP, HW = 4, FX = L::FX;
+  __shared__ Rows2<T2::ROWS> zn;
+  extern __shared__ __align__(16) char smem[];
+  double* tile = reinterpret_cast<double*>(smem);
+  double* Tt = tile + 4 * TSZ;                       // p / rho
+  double* carr = Tt + TSZ;
+  CT* txx = reinterpret_cast<CT*>(carr);             // x -2..34, y 0..16
+  CT* qx = txx + L::NXX;
+  CT* tyy = qx + L::NXX;                             // x 0..32, y -2..18
+  CT* qy = tyy + L::NYY;
+  CT* txy = qy + L::NYY;                             // x -2..34, y -2..18
+  const XcdWork it(NPART * A.topo.h.n_blocks);       // one work item per workgroup
+  if (!it.ok()) return;
+  const int tid = threadIdx.x, part = it.w % NPART;
+  const int b = A.order ? A.topo.list()[it.w / NPART] : it.w / NPART;
+  const BlockDesc d = A.topo.blk()[b];
+  const int y0 = part * NSY, cnty = min(NSY, NB - y0);
+  row_table<NB, 4, NST>(zn, d, A.topo.nb(b), A.topo.h.nb_stride, y0 - T2::H);
+  const int base = d.slot * 4 * NP;
+  {
+    G g;
+    const StageValue<double> val{A.alpha, A.off};
+    with_source<KT>(A, [&](const auto& src) { g.run(carr, zn, base, d.n_coarse > 0, y0, cnty, src, val); });
+#pragma unroll
+    for (int i = 0; i < T2::NR; ++i) {
+      if (!((g.in >> i) & 1u)) continue;
+      const int q = g.x + TW * (g.rg + T2::RG * i);
+#pragma unroll
+      for (int f = 0; f < 4; ++f) tile[f * TSZ + q] = g.v[i][f];
+      Tt[q] = g.v[i][3] / g.v[i][0];
+    }
+  }
+  __syncthreads();
+  CT mu, kap, gam, c23, r;
+  mu = (CT)A.ph.mu;
+  kap = (CT)A.ph.kap;
+  gam = (CT)A.ph.gamma;
+  c23 = (CT)(2.0 / 3.0);
+  if constexpr (sizeof(CT) == 8) r = A.lt.r[d.level];
+  else r = A.lt.rf[d.level];
+  const double *fr = tile, *fu = tile + TSZ, *fv = tile + 2 * TSZ, *fp = tile + 3 * TSZ;
+  auto Dx = [&](const double* F, int q) { return D4d<CT>(F[q - 2], F[q - 1], F[q + 1], F[q + 2], r); };
+  auto Dy = [&](const double* F, int q) { return D4d<CT>(F[q - 2 * TW], F[q - TW], F[q + TW], F[q + 2 * TW], r); };
+  // Stresses and heat flux, each where a derivative along x or y reads it: at the thread's
+  // own node, whose velocity gradients, stresses and momentum factors stay in registers for
+  // the right-hand side, then at the points beside the region (two per side and row).
+  static_assert(NB * NSY <= NST, "one region node per thread");
+  const int nn = NB * cnty;
+  const bool mine = tid < nn;
+  const int ly = mine ? tid / NB : 0, lx = mine ? tid - ly * NB : 0;
+  const int q = lx + HW + TW * (ly + HW);
+  const int wx = lx + 2 + FX * ly, wy = lx + NB * (ly + 2), wc = lx + 2 + FX * (ly + 2);
+  CT ux, uy, vx, vy, sxx, syy, sxy;
+  double um[4], vm[4];   // u along x, v along y (the momentum derivatives' factors)
+  if (mine) {
+    um[0] = fu[q - 2]; um[1] = fu[q - 1]; um[2] = fu[q + 1]; um[3] = fu[q + 2];
+    vm[0] = fv[q - 2 * TW]; vm[1] = fv[q - TW]; vm[2] = fv[q + TW]; vm[3] = fv[q + 2 * TW];
+    ux = D4d<CT>(um[0], um[1], um[2], um[3], r);
+    vy = D4d<CT>(vm[0], vm[1], vm[2], vm[3], r);
+    uy = Dy(fu, q);
+    vx = Dx(fv, q);
+    const CT div = ux + vy;
+    sxx = mu * (CT(2) * ux - c23 * div);
+    syy = mu * (CT(2) * vy - c23 * div);
+    sxy = mu * (uy + vx);
+    txx[wx] = sxx;
+    tyy[wy] = syy;
+    txy[wc] = sxy;
+    qx[wx] = -(kap * Dx(Tt, q));
+    qy[wy] = -(kap * Dy(Tt, q));
+  }
+  {
+    const int p = NST - 1 - tid;                     // the last waves have fewer own nodes
+    const int nside = 4 * cnty;
+    if (p < nside + 4 * NB) {
+      const bool xs = p < nside;                     // beside the region along x
+      const int k = xs ? p % 4 : (p - nside) / NB;
+      const int fx = xs ? (k < 2 ? k - 2 : NB - 2 + k) : (p - nside) % NB;
+      const int fy = xs ? p / 4 : (k < 2 ? k - 2 : cnty - 2 + k);
+      const int s = fx + HW + TW * (fy + HW);
+      const CT ax = Dx(fu, s), ay = Dy(fu, s), bx = Dx(fv, s), by = Dy(fv, s);
+      const CT div = ax + by;
+      txy[fx + 2 + FX * (fy + 2)] = mu * (ay + bx);
+      if (xs) {
+        txx[fx + 2 + FX * fy] = mu * (CT(2) * ax - c23 * div);
+        qx[fx + 2 + FX * fy] = -(kap * Dx(Tt, s));
+      } else {
+        tyy[fx + NB * (fy + 2)] = mu * (CT(2) * by - c23 * div);
+        qy[fx + NB * (fy + 2)] = -(kap * Dy(Tt, s));
+      }
+    }
+  }
+  __syncthreads();
+  if (mine) {
+    const size_t node = (size_t)base + lx + NB * (y0 + ly);
+    const CT rho = (CT)fr[q], uu = (CT)fu[q], vv = (CT)fv[q], pp = (CT)fp[q];
+    const CT px = Dx(fp, q), py = Dy(fp, q);
+    const CT dmx = D4d<CT>(fr[q - 2] * um[0], fr[q - 1] * um[1], fr[q + 1] * um[2], fr[q + 2] * um[3], r);
+    const CT dmy = D4d<CT>(fr[q - 2 * TW] * vm[0], fr[q - TW] * vm[1], fr[q + TW] * vm[2], fr[q + 2 * TW] * vm[3], r);
+    auto dxw = [&](const CT* w, int i) { return D4(w[i - 2], w[i - 1], w[i + 1], w[i + 2], r); };
+    auto dyw = [&](const CT* w, int i, int s) { return D4(w[i - 2 * s], w[i - s], w[i + s], w[i + 2 * s], r); };
+    const CT dtxx = dxw(txx, wx), dtxy_y = dyw(txy, wc, FX), dtxy_x = dxw(txy, wc), dtyy = dyw(tyy, wy, NB);
+    const CT dqx = dxw(qx, wx), dqy = dyw(qy, wy, NB);
+    CT kv[4];
+    kv[0] = -(dmx + dmy);
+    kv[1] = -(uu * ux + vv * uy) - px / rho + (dtxx + dtxy_y) / rho;
+    kv[2] = -(uu * vx + vv * vy) - py / rho + (dtxy_x + dtyy) / rho;
+    const CT phi = sxx * ux + sxy * (uy + vx) + syy * vy;
+    const CT divq = dqx + dqy;
+    kv[3] = -(uu * px + vv * py) - gam * pp * (ux + vy) + (gam - CT(1)) * (phi - divq);
+    if (A.stage < 4) {
+#pragma unroll
+      for (int f = 0; f < 4; ++f) ((KT*)A.kout + f * NP)[node] = (KT)kv[f];
+    } else {
+      // The update's operands, requested together once the right-hand side's registers are
+      // free (held through it they cost more in resident waves than their latency does)
+      __builtin_amdgcn_sched_barrier(0);
+      KT e1[4], e2[4], e3[4];
+      double eu[4];
+#pragma unroll
+      for (int f = 0; f < 4; ++f) {
+        e1[f] = ((const KT*)A.k1 + f * NP)[node];
+        e2[f] = ((const KT*)A.k2 + f * NP)[node];
+        e3[f] = ((const KT*)A.k3 + f * NP)[node];
+        eu[f] = (A.u + f * NP)[node];
+      }
+#pragma unroll
+      for (int f = 0; f < 4; ++f)
+        (A.unew + f * NP)[node] = eu[f] + A.h6 * (((double)e1[f] + (double)kv[f]) + 2.0 * ((double)e2[f] + (double)e3[f]));
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Shock-capturing filter after a time step (formulas at FilterArgs), half a block per
+// workgroup: per axis the pressure sensor of one point more than the region on either side,
+// then the switched second-order fluxes.  2,944 blocks: 58 us (205 MB of block data,
+// 3.5 TB/s) against 149 us for whole blocks of 256 threads, one per compute unit.
+// ---------------------------------------------------------------------------
+constexpr int FHW = 3;   // p is read up to 3 beyond the region, the other fields 1
+
+struct FilterLds {
+  using T2 = Tile2<NB, 4, FHW, NSY, NST>;
+  static constexpr int SX = (NB + 2) * NSY, SY = NB * (NSY + 2);
+  static constexpr size_t tile = sizeof(double) * 4 * T2::TSZ, sens = sizeof(double) * (SX + SY),
+                          lat = sizeof(double) * 2 * 4 * T2::CSZ;
+  static constexpr size_t bytes = tile + (sens > lat ? sens : lat);   // (the lattice is dead before the sensors)
+};
+
+struct FilterValue {
+  __device__ __forceinline__ double operator()(double u, int) const { return u; }
+};
+
+__global__ void __launch_bounds__(NST) k_filter2(FilterArgs A) {
+  using G = Gather2<NB, 4, FHW, NSY, NST, double>;
+  using T2 = typename G::T2;
+  constexpr int TW = T2::TW, TSZ = T2::TSZ, NP = T2::NP, SXW = NB + 2;
+  __shared__ Rows2<T2::ROWS> zn;
+  extern __shared__ __align__(16) char smem[];
+  double* tile = reinterpret_cast<double*>(smem);
+  double* carr = tile + 4 * TSZ;
+  double* sx = carr;                     // sensor along x at x = -1..33, y = 0..cnt-1
+  double* sy = sx + FilterLds::SX;       // sensor along y at x = 0..32, y = -1..cnt
+  const XcdWork it(NPART * A.topo.h.n_blocks);
+  if (!it.ok()) return;
+  const int tid = threadIdx.x, part = it.w % NPART, b = it.w / NPART;
+  const BlockDesc d = A.topo.blk()[b];
+  const int y0 = part * NSY, cnty = min(NSY, NB - y0);
+  row_table<NB, 4, NST>(zn, d, A.topo.nb(b), A.topo.h.nb_stride, y0 - T2::H);
+  const int base = d.slot * 4 * NP;
+  {
+    G g;
+    g.run(carr, zn, base, d.n_coarse > 0, y0, cnty, LoadU{A.u}, FilterValue{});
+#pragma unroll
+    for (int i = 0; i < T2::NR; ++i) {
+      if (!((g.in >> i) & 1u)) continue;
+#pragma unroll
+      for (int f = 0; f < 4; ++f) tile[f * TSZ + g.x + TW * (g.rg + T2::RG * i)] = g.v[i][f];
+    }
+  }
+  __syncthreads();
+  const double* P = tile + 3 * TSZ;
+  auto sens = [&](int q, int st) -> double {
+    auto Dp = [&](int c) { return ((-P[c + st] + 2.0 * P[c]) - P[c - st]) * 0.25; };
+    const double d0 = Dp(q), dp = Dp(q + st), dm = Dp(q - st);
+    const double m = ((d0 - dp) * (d0 - dp) + (d0 - dm) * (d0 - dm)) * 0.5;
+    const double p0 = P[q];
+    const double r = m / (p0 * p0) + 1e-16;
+    const double sv = 1.0 - A.rth / r;
+    return sv > 0.0 ? sv : 0.0;
+  };
+  for (int p = tid; p < SXW * cnty + NB * (cnty + 2); p += NST) {
+    if (p < SXW * cnty) {
+      const int y = p / SXW, x = p - y * SXW;
+      sx[p] = sens(x - 1 + FHW + TW * (y + FHW), 1);
+    } else {
+      const int r = p - SXW * cnty, y = r / NB, x = r - y * NB;
+      sy[r] = sens(x + FHW + TW * (y - 1 + FHW), TW);
+    }
+  }
+  __syncthreads();
+  if (tid < NB * cnty) {
+    const int y = tid / NB, x = tid - y * NB;
+    const double sx0 = sx[(x + 1) + SXW * y], sy0 = sy[x + NB * (y + 1)];
+    const double sxm = (sx[x + SXW * y] + sx0) * 0.5, sxp = (sx0 + sx[(x + 2) + SXW * y]) * 0.5;
+    const double sym = (sy[x + NB * y] + sy0) * 0.5, syp = (sy0 + sy[x + NB * (y + 2)]) * 0.5;
+    const double* Q = tile + x + FHW + TW * (y + FHW);
+    double* out = A.unew + (size_t)base + x + NB * (y0 + y);
+#pragma unroll
+    for (int f = 0; f < 4; ++f, Q += TSZ) {
+      const double q = Q[0];
+      const double fxp = -(Q[1] - q) * 0.25, fxm = -(q - Q[-1]) * 0.25;
+      const double fyp = -(Q[TW] - q) * 0.25, fym = -(q - Q[-TW]) * 0.25;
+      out[f * NP] = q - ((sxp * fxp - sxm * fxm) + (syp * fyp - sym * fym));
+    }
+  }
+}
+
+// one workgroup per work item (XcdWork deals them out from a multiple of 8)
+template <typename K, typename Arg>
+hipError_t go2(K kern, int items, size_t lds, int threads, hipStream_t st, const Arg& a) {
+  if (lds > 65536) {
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kern, dim3(std::max(8, (items + 7) & ~7)), dim3(threads), lds, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_stage2(const Shape& s, int precision, const StageArgs& a, hipStream_t st) {
+  const int n = a.topo.h.n_blocks;
+  if (s.nf == 4) {
+    if (precision == 0) return go2(k_stage_ns<double, double>, NPART * n, NsLds<double, double>::bytes, NST, st, a);
+    return go2(k_stage_ns<float, float>, NPART * n, NsLds<float, float>::bytes, NST, st, a);
+  }
+  if (s.bs == 33) {
+    if (precision == 0) return go2(k_stage2<33, 576, double, double>, n, 0, 576, st, a);
+    return go2(k_stage2<33, 576, float, float>, n, 0, 576, st, a);
+  }
+  if (precision == 0) return go2(k_stage2<17, 448, double, double>, n, 0, 448, st, a);
+  return go2(k_stage2<17, 448, float, float>, n, 0, 448, st, a);
+}
+
+hipError_t launch_filter(const FilterArgs& a, hipStream_t st) {
+  return go2(k_filter2, NPART * a.topo.h.n_blocks, FilterLds::bytes, NST, st, a);
+}
+
+}  // namespace mrb

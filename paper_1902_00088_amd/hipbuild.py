@@ -20,7 +20,7 @@ HIPFLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contrac
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objs, procs = [], []
-    for src in ("kernels.hip", "column3.hip", "topo.hip", "mlp.hip", "mrb.cpp"):   # compiled side by side
+    for src in ("kernels.hip", "column3.hip", "plane2.hip", "topo.hip", "mlp.hip", "mrb.cpp"):   # compiled side by side
         obj = os.path.join(CSRC, src.rsplit(".", 1)[0] + ".o")
         lang = ["-x", "hip"] if src.endswith(".hip") else []
         cmd = [hipcc] + HIPFLAGS + lang + ["-c", os.path.join(CSRC, src), "-o", obj]

@@ -1130,3 +1130,43 @@ def test_3d_column_kernels_on_ragged_forests(seed, p_refine, jmin):
         mixed.append(s.read_blocks())
         s.close()
     assert np.array_equal(mixed[0], mixed[1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("which", ["C1", "C2", "C2t", "C3", "DSL"])
+@pytest.mark.parametrize("seed,p_refine", [(0, 0.45), (2, 0.3), (4, 0.7)])
+def test_2d_zone_kernels_on_ragged_forests(which, seed, p_refine):
+    """The default 2D stages (owners per zone; halves of blocks for Navier-Stokes) and the
+    filter on random graded forests: FP64 bitwise against the oracle, mixed bitwise against
+    the sub-tiled kernels (the same operations per point)."""
+    make = {"C1": W.C1, "C2": W.C2, "C2t": W.C2, "C3": W.C3, "DSL": W.DSL}[which]
+    cfg = make(jmax=5, form=W.FORM_FUSED, max_blocks=2000)
+    if which == "C2t":
+        cfg = cfg.replace(phys=(5.0,))
+    lv, co = W.random_graded_forest(2, 4, seed, p_refine)
+    s, o = M.Solver(cfg), oracle.Oracle(cfg)
+    o.init_forest(lv, co)
+    lv, co = o.read_forest()
+    data = W.sample(cfg, lv, co)
+    s.init_forest(lv, co)
+    s.load_blocks(data)
+    o.load_blocks(data)
+    zoned = {"C1": 448}.get(which, 576)
+    assert s.stats()["stage_threads"] == (zoned if which == "C1" or len(lv) > 16 else 256)
+    for k in range(2):
+        s.rk4(k * cfg.dt, cfg.dt)
+        o.rk4(k * cfg.dt, cfg.dt)
+    assert np.array_equal(s.read_blocks(), o.read_blocks())
+    s.close()
+    mixed = []
+    for force in (0, 2):
+        s = M.Solver(cfg.replace(precision=W.MIXED))
+        s.init_forest(lv, co)
+        s.load_blocks(data)
+        if force:
+            s.tune(nsub=force)
+        for k in range(2):
+            s.rk4(k * cfg.dt, cfg.dt)
+        mixed.append(s.read_blocks())
+        s.close()
+    assert np.array_equal(mixed[0], mixed[1])
