@@ -237,7 +237,7 @@ hipError_t launch_plain(const Shape& s, int grid, const StageArgs& a, hipStream_
 // with the analysis only; mothers: the second analysis of a speculated coarsening that
 // merges every block, with refine only)
 hipError_t launch_rk4t(const Shape& s, int precision, int nsub, bool analysis, bool refine, bool mothers, int tpb,
-                       int grid, const Rk4tArgs& a, hipStream_t st);
+                       const Rk4tArgs& a, hipStream_t st);
 int rk4t_variants(const Shape& s, int precision, int* nsub, int cap);
 hipError_t launch_mr(const Shape& s, int nsub, int tpb, int grid, const MrArgs& a, hipStream_t st);
 int mr_threads(const Shape& s, int nsub, int* tpb, int cap);   // compiled workgroup sizes (256 first)

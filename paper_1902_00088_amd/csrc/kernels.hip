@@ -868,12 +868,21 @@ __global__ void __launch_bounds__(256) k_sweep(SweepArgs S) {
 // E points and evaluates k1 on the region + E - HW, k2 on + E - 2 HW, ... -- the halo
 // work repeats, with the same operations in the same order, what the neighbours
 // compute at their own nodes, so the result is bitwise the four stage launches'.
-// k1..k3 stay in LDS; HBM sees u read once and u_new written once.  With ANA the
+// HBM sees u read once and u_new written once.  With ANA the
 // halo is 3 points wider, u_new is known up to 3 points beyond the region, and the
 // workgroup also runs the analysis of u_new (Sec. 2.3): details, their maxima, the
 // flag, and the speculated mothers' nodes, as the analysis kernel does for a forest
 // on one level (no finer neighbour, so no redundant node to write back).  A missing
 // neighbour (a forest not on one level) yields NaN.
+//
+// A thread keeps the same tile points through the four stages, with their u, slopes and
+// velocity products in registers, so LDS holds two stage-value arrays only (38 KB in FP64
+// for a whole block, 84 KB with u and the slopes in LDS) and a point reads its eight
+// neighbours and nothing else per stage.  Vector issue and LDS reads bound large forests
+// (60% each): 4,096 whole blocks of 33^2 in FP64 take 56 us with 512 threads against 217 us
+// with everything in LDS and 256.  Threads that own vertical strips instead read less LDS
+// but computed more of the halo (63 us).  Small forests are bound by the launch's chain of
+// latencies: the 64-block folded step takes 9.9 us against 11.8.
 // ---------------------------------------------------------------------------
 // NaN-propagating maxima of two values over a workgroup of TPB threads (values as for
 // wave_nanmax): wave maxima through red (2 TPB / 64 doubles of LDS; a barrier must lie
@@ -901,11 +910,13 @@ struct TileGeo {
   // children (3) or on the mothers (6 child nodes)
   static constexpr int HW = 2, E = 4 * HW + (MA ? 6 : (ANA ? 3 : 0));
   static constexpr int S = (BS + NSUB - 1) / NSUB, TW = S + 2 * E, TSZ = TW * TW;
-  // slopes are kept where the last stage combines them: the region + E - 4 HW
-  static constexpr int KW = S + 2 * (E - 4 * HW), KSZ = KW * KW;
-  // LDS bytes: u (FP64), three slope arrays, two stage-value arrays
-  template <typename TT, typename KT>
-  static constexpr size_t lds() { return (size_t)TSZ * sizeof(double) + 3 * (size_t)KSZ * sizeof(KT) + 2 * (size_t)TSZ * sizeof(TT); }
+  static constexpr int YS = (TSZ + 1) & ~1;   // stage-value array stride (FP64 values share its LDS)
+  // LDS bytes: two stage-value arrays, and in the mixed form with the analysis u (FP64;
+  // otherwise u shares the first stage-value array, or stays in registers)
+  template <typename TT>
+  static constexpr size_t lds() {
+    return 2 * (size_t)YS * sizeof(TT) + (ANA && sizeof(TT) == 4 ? (size_t)TSZ * sizeof(double) : 0);
+  }
 };
 
 // Every node of [lo, lo + n) in the 2D parity classes C0..3 in one pass, each class on
@@ -988,252 +999,284 @@ struct MotherDetails {
 };
 
 template <int BS, int NSUB, typename TT, typename KT, bool ANA, int TPB, bool REF = false, bool MA = false>
-__global__ void __launch_bounds__(TPB) k_rk4t(Rk4tArgs A) {
+__global__ void __launch_bounds__(TPB, TPB >= 512 ? 4 : 2) k_rk4t(Rk4tArgs A) {
   static_assert(!MA || (ANA && REF), "the mothers' analysis comes with the folded refinement");
   using TG = TileGeo<BS, NSUB, ANA, MA>;
   constexpr int HW = TG::HW, E = TG::E, S = TG::S, TW = TG::TW, TSZ = TG::TSZ, NP = BS * BS;
   constexpr int NSUBT = NSUB * NSUB;
   using G = Geo<2, BS, S, E>;
   static_assert(G::TW == TW, "tile geometry");
-  static_assert(S + 2 * (E - HW) <= 64 && (S + 2 * (E - HW)) * (S + 2 * (E - HW)) < 4096,
-                "the stage loops' float row split needs rows of at most 64 points, fewer than 2^12 in all");
-  constexpr int KW = TG::KW, KSZ = TG::KSZ, KO = E - 4 * HW;   // slope zone: tile index - (E - KO)
+  // Tile points per thread, the same ones in every stage: a point's u, slopes and velocity
+  // products stay in its thread's registers, and LDS carries stage values only.
+  constexpr int NPT = (TSZ + TPB - 1) / TPB;
   extern __shared__ __align__(16) char smem[];
-  double* U = reinterpret_cast<double*>(smem);
-  KT* K = reinterpret_cast<KT*>(U + TSZ);          // k1, k2, k3 on the slope zone
-  TT* Ya = reinterpret_cast<TT*>(K + 3 * KSZ);     // stage values: this stage's and the next
-  TT* Yb = Ya + TSZ;
+  TT* Ya = reinterpret_cast<TT*>(smem);            // stage values: this stage's and the next
+  TT* Yb = Ya + TG::YS;
+  // u before the step (REF) and after it (ANA), FP64
+  double* U = sizeof(TT) == 8 ? reinterpret_cast<double*>(Ya) : reinterpret_cast<double*>(Yb + TG::YS);
   __shared__ int tab[9];                            // same-level holder by direction
   __shared__ double sw[4 * TW];
   __shared__ double red[2 * (TPB / 64)];
   const int nblk = A.topo.h.n_blocks;
   const BlockDesc* blk = A.topo.blk();
   const int tid = threadIdx.x;
-  for (XcdWork it(nblk * NSUBT); it.ok(); it.next()) {
-    const int b = it.w / NSUBT;
-    // everything the work item's addresses depend on, requested at once: the block, its
-    // (or, with REF, its parent's) entry row up to the row stride -- entries past the
-    // count are ignored --, the speculation map and the refinement plan's child slot
-    const int ri = b >> 2, ch = b & 3;
-    const BlockDesc d = blk[b];
-    const BlockDesc P = REF ? A.topo.pblk()[ri] : d;
-    const NbEntry* ent = REF ? A.topo.pnb(ri) : A.topo.nb(b);
-    const int erow = REF ? A.topo.h.pnb_stride : A.topo.h.nb_stride;
-    NbEntry q0;
-    if (tid < erow) q0 = ent[tid];
-    const int sm = ANA && A.smap ? A.smap[b] : -1;
-    const int kslot = REF ? A.topo.ref()[ri].child[ch] : -1;
-    int r0[3], cnt[3];
-    subregion<2>(it.w % NSUBT, NSUB, S, BS, r0, cnt);
-    if (tid < 9) tab[tid] = -1;
+  const XcdWork it(nblk * NSUBT);   // one work item per workgroup
+  if (!it.ok()) return;
+  const int b = it.w / NSUBT;
+  // everything the work item's addresses depend on, requested at once: the block, its
+  // (or, with REF, its parent's) entry row up to the row stride -- entries past the
+  // count are ignored --, the speculation map and the refinement plan's child slot
+  const int ri = b >> 2, ch = b & 3;
+  const BlockDesc d = blk[b];
+  const BlockDesc P = REF ? A.topo.pblk()[ri] : d;
+  const NbEntry* ent = REF ? A.topo.pnb(ri) : A.topo.nb(b);
+  const int erow = REF ? A.topo.h.pnb_stride : A.topo.h.nb_stride;
+  NbEntry q0;
+  if (tid < erow) q0 = ent[tid];
+  const int sm = ANA && A.smap ? A.smap[b] : -1;
+  const int kslot = REF ? A.topo.ref()[ri].child[ch] : -1;
+  int r0[3], cnt[3];
+  subregion<2>(it.w % NSUBT, NSUB, S, BS, r0, cnt);
+  if (tid < 9) tab[tid] = -1;
+  __syncthreads();
+  // same-level holders by direction
+  auto take = [&](const NbEntry& q) {
+    const int ox = q.o[0], oy = q.o[1];
+    if (q.dl == 0 && ox % (BS - 1) == 0 && oy % (BS - 1) == 0 && ox >= -(BS - 1) && ox <= BS - 1 &&
+        oy >= -(BS - 1) && oy <= BS - 1)
+      tab[(oy / (BS - 1) + 1) * 3 + ox / (BS - 1) + 1] = q.slot;
+  };
+  if (tid < P.n_ent) take(q0);
+  for (int e = tid + TPB; e < P.n_ent; e += TPB) take(ent[e]);
+  __syncthreads();
+  // swirl table slices (first read by the first stage, several barriers on)
+  if (A.ph.kind == 1) {
+    const int nl = A.lt.nl[d.level], shift = A.ph.jmax - d.level;
+    for (int q = tid; q < 4 * TW; q += blockDim.x) {
+      const int k = q / TW, l = q % TW, ax = k / 2;
+      int gg = d.c[ax] * (BS - 1) + r0[ax] - E + l;
+      gg = gg < 0 ? gg + nl : (gg >= nl ? gg - nl : gg);
+      gg <<= shift;
+      sw[q] = (k & 1) ? A.ph.s[gg] : A.ph.s2[gg];
+    }
+  }
+  // the thread's points: distance to the tile's edge (the halo a stage consumes), the
+  // swirl's velocity products (their LDS reads overlap the tile's set-up)
+  const int nx = cnt[0] + 2 * E, ny = cnt[1] + 2 * E;
+  const bool swirl = A.ph.kind == 1;
+  double u[NPT], pu[NPT], pw[NPT];
+  KT k1[NPT];
+  double s23[NPT];
+  int edge[NPT];
+  auto point_setup = [&]() {
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) {
+      const int p = min(tid + i * TPB, TSZ - 1), iy = p / TW, ix = p - iy * TW;
+      edge[i] = tid + i * TPB < TSZ ? min(min(ix, nx - 1 - ix), min(iy, ny - 1 - iy)) : -1;
+      pu[i] = pw[i] = 0.0;
+      if (swirl) {
+        pu[i] = sw[ix] * sw[3 * TW + iy];
+        pw[i] = sw[2 * TW + iy] * sw[TW + ix];
+      }
+    }
+  };
+  // stage values as the stage kernels' gather forms them: y = u + alpha k_{s-1} (in
+  // FP64, from the stored slope), minus the field offset in FP32 tiles
+  auto stage_value = [&](double y) -> TT {
+    if constexpr (sizeof(TT) == 4) return (TT)(y - A.off);
+    else return y;
+  };
+  if constexpr (REF) {
+    // The refinement of a forest on one level folded in: the tile is built from the
+    // parents.  Block b is child b % 4 of refinement work b / 4 (every parent refines,
+    // so children follow their parents in forest order), and a child point takes the
+    // synchronised value at the children's level on the parents' grid -- the parent's
+    // value at even points, its prediction elsewhere -- as the refinement kernel
+    // computes it; the children's pre-step values never reach HBM.
+    // Parent-level values over the fine box [r0 + cb - E, r0 + cb + cnt - 1 + E] and
+    // the prediction's reach (3 fine points), in the second stage-value array (a
+    // quarter of its bytes; unused until the first stage's pass)
+    double* PT = reinterpret_cast<double*>(Yb);
+    const bool own = kslot == d.slot;
+    int cb[2], plo[2], pw[2];
+    for (int a = 0; a < 2; ++a) {
+      cb[a] = ((ch >> a) & 1) * (BS - 1);
+      plo[a] = (r0[a] + cb[a] - E - 3) >> 1;
+      pw[a] = ((r0[a] + cb[a] + cnt[a] - 1 + E + 3) >> 1) - plo[a] + 1;
+    }
+    const float rpw = 1.0f / (float)pw[0];
+    for (int p = tid; p < pw[0] * pw[1]; p += blockDim.x) {
+      const int qy = fdiv(p, rpw);
+      const int px = plo[0] + p - qy * pw[0], py = plo[1] + qy;
+      const int dx = px < 0 ? 0 : (px > BS - 1 ? 2 : 1), dy = py < 0 ? 0 : (py > BS - 1 ? 2 : 1);
+      const int slot = own ? tab[dy * 3 + dx] : -1;
+      const int lx = px - (dx - 1) * (BS - 1), ly = py - (dy - 1) * (BS - 1);
+      PT[p] = slot >= 0 ? A.u[(size_t)slot * NP + lx + BS * ly] : __builtin_nan("");
+    }
     __syncthreads();
-    // same-level holders by direction
-    auto take = [&](const NbEntry& q) {
-      const int ox = q.o[0], oy = q.o[1];
-      if (q.dl == 0 && ox % (BS - 1) == 0 && oy % (BS - 1) == 0 && ox >= -(BS - 1) && ox <= BS - 1 &&
-          oy >= -(BS - 1) && oy <= BS - 1)
-        tab[(oy / (BS - 1) + 1) * 3 + ox / (BS - 1) + 1] = q.slot;
+    point_setup();   // (sw is visible since the barrier)
+    // the children's values on the fine box, a quad of fine points (2X + {0, 1},
+    // 2Y + {0, 1}) per thread: the parent's value, its prediction along x, along y and
+    // along both, each as the refinement kernel's per-class tensor stencil forms it (the
+    // quad shares the parent values and the x-prediction of row Y)
+    int qlo[2], qhi[2], x0[2], nq[2];
+    for (int a = 0; a < 2; ++a) {
+      qlo[a] = r0[a] + cb[a] - E;
+      qhi[a] = qlo[a] + cnt[a] + 2 * E - 1;
+      x0[a] = qlo[a] >> 1;
+      nq[a] = (qhi[a] >> 1) - x0[a] + 1;
+    }
+    auto pt = [&](int X, int Y) { return PT[(X - plo[0]) + pw[0] * (Y - plo[1])]; };
+    auto put = [&](int qx, int qy, double v) {
+      const int i = G::idx(qx - qlo[0], qy - qlo[1], 0);
+      U[i] = v;
+      if (sizeof(TT) == 4) Ya[i] = stage_value(v);   // (in FP64 the same array)
     };
-    if (tid < P.n_ent) take(q0);
-    for (int e = tid + TPB; e < P.n_ent; e += TPB) take(ent[e]);
-    __syncthreads();
-    // swirl table slices (first read by the first stage, several barriers on)
-    if (A.ph.kind == 1) {
-      const int nl = A.lt.nl[d.level], shift = A.ph.jmax - d.level;
-      for (int q = tid; q < 4 * TW; q += blockDim.x) {
-        const int k = q / TW, l = q % TW, ax = k / 2;
-        int gg = d.c[ax] * (BS - 1) + r0[ax] - E + l;
-        gg = gg < 0 ? gg + nl : (gg >= nl ? gg - nl : gg);
-        gg <<= shift;
-        sw[q] = (k & 1) ? A.ph.s[gg] : A.ph.s2[gg];
+    auto row = [&](int X, int Y) { return P4(pt(X - 1, Y), pt(X, Y), pt(X + 1, Y), pt(X + 2, Y)); };
+    const float rnq = 1.0f / (float)nq[0];
+    for (int p = tid; p < nq[0] * nq[1]; p += blockDim.x) {
+      const int qy = fdiv(p, rnq);
+      const int X = x0[0] + p - qy * nq[0], Y = x0[1] + qy;
+      const bool ex = 2 * X >= qlo[0], ox = 2 * X + 1 <= qhi[0];
+      const bool ey = 2 * Y >= qlo[1], oy = 2 * Y + 1 <= qhi[1];
+      if (ex && ey) put(2 * X, 2 * Y, pt(X, Y));
+      if (ex && oy) put(2 * X, 2 * Y + 1, P4(pt(X, Y - 1), pt(X, Y), pt(X, Y + 1), pt(X, Y + 2)));
+      if (ox) {
+        const double ry = row(X, Y);
+        if (ey) put(2 * X + 1, 2 * Y, ry);
+        if (oy) put(2 * X + 1, 2 * Y + 1, P4(row(X, Y - 1), ry, row(X, Y + 1), row(X, Y + 2)));
       }
     }
-    // stage values as the stage kernels' gather forms them: y = u + alpha k_{s-1} (in
-    // FP64, from the stored slope), minus the field offset in FP32 tiles
-    auto stage_value = [&](double y) -> TT {
-      if constexpr (sizeof(TT) == 4) return (TT)(y - A.off);
-      else return y;
-    };
-    if constexpr (REF) {
-      // The refinement of a forest on one level folded in: the tile is built from the
-      // parents.  Block b is child b % 4 of refinement work b / 4 (every parent refines,
-      // so children follow their parents in forest order), and a child point takes the
-      // synchronised value at the children's level on the parents' grid -- the parent's
-      // value at even points, its prediction elsewhere -- as the refinement kernel
-      // computes it; the children's pre-step values never reach HBM.
-      // Parent-level values over the fine box [r0 + cb - E, r0 + cb + cnt - 1 + E] and
-      // the prediction's reach (3 fine points), in the second stage-value array (a
-      // quarter of its bytes; unused until the first stage's pass)
-      double* PT = reinterpret_cast<double*>(Yb);
-      const bool own = kslot == d.slot;
-      int cb[2], plo[2], pw[2];
-      for (int a = 0; a < 2; ++a) {
-        cb[a] = ((ch >> a) & 1) * (BS - 1);
-        plo[a] = (r0[a] + cb[a] - E - 3) >> 1;
-        pw[a] = ((r0[a] + cb[a] + cnt[a] - 1 + E + 3) >> 1) - plo[a] + 1;
+  }
+  if constexpr (!REF) {
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) {
+      const int p = min(tid + i * TPB, TSZ - 1), iy = p / TW, ix = p - iy * TW;
+      const int tx = r0[0] - E + ix, ty = r0[1] - E + iy;
+      const int dx = tx < 0 ? 0 : (tx > BS - 1 ? 2 : 1), dy = ty < 0 ? 0 : (ty > BS - 1 ? 2 : 1);
+      // (points past a smaller sub-tile's halo may lie beyond the neighbours: they load
+      // the block's first node and take part in no stage)
+      const bool in = ix < nx && iy < ny;
+      const int slot = in ? tab[dy * 3 + dx] : -1;
+      const int lx = tx - (dx - 1) * (BS - 1), ly = ty - (dy - 1) * (BS - 1);
+      const double v = A.u[slot >= 0 ? (size_t)slot * NP + lx + BS * ly : (size_t)d.slot * NP];
+      u[i] = slot >= 0 ? v : __builtin_nan("");
+    }
+#pragma unroll
+    for (int i = 0; i < NPT; ++i)
+      if (tid + i * TPB < TSZ) Ya[tid + i * TPB] = stage_value(u[i]);
+  }
+  __syncthreads();
+  if constexpr (REF) {
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) u[i] = U[min(tid + i * TPB, TSZ - 1)];
+  } else {
+    point_setup();
+  }
+  TT r;
+  if constexpr (sizeof(TT) == 8) r = A.lt.r[d.level];
+  else r = A.lt.rf[d.level];
+  const TT c0 = (TT)A.ph.c[0], c1 = (TT)A.ph.c[1];
+  // With up to two points per thread (small forests: latency) every point runs every stage
+  // without a branch, a point outside the stage's zone at the tile's centre, so the points'
+  // reads overlap; with more (throughput) points outside the zone are skipped.
+  constexpr bool BRANCHLESS = NPT <= 2;
+#pragma unroll
+  for (int s = 1; s <= 4; ++s) {
+    // k_s within E - s HW of the region, and in the same pass the next stage's values
+    // there; the last stage forms u_new and stores it on the region
+    const TT* Y = (s & 1) ? Ya : Yb;
+    TT* Yn = (s & 1) ? Yb : Ya;
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) {
+      const bool act = edge[i] >= HW * s;
+      if (!BRANCHLESS && !act) continue;
+      const int q = tid + i * TPB;
+      const TT* T = Y + (BRANCHLESS && !act ? (TW / 2) * (TW + 1) : q);
+      const TT dx = D4(T[-2], T[-1], T[1], T[2], r);
+      const TT dy = D4(T[-2 * TW], T[-TW], T[TW], T[2 * TW], r);
+      TT kv;
+      if (swirl) {
+        const double vu = pu[i] * A.cfac[s - 1], vw = -(pw[i] * A.cfac[s - 1]);
+        kv = -(((TT)vu * dx) + ((TT)vw * dy));
+      } else {
+        TT acc = c0 * dx;
+        acc = acc + c1 * dy;
+        kv = -acc;
       }
-      const float rpw = 1.0f / (float)pw[0];
-      for (int p = tid; p < pw[0] * pw[1]; p += blockDim.x) {
-        const int qy = fdiv(p, rpw);
-        const int px = plo[0] + p - qy * pw[0], py = plo[1] + qy;
-        const int dx = px < 0 ? 0 : (px > BS - 1 ? 2 : 1), dy = py < 0 ? 0 : (py > BS - 1 ? 2 : 1);
-        const int slot = own ? tab[dy * 3 + dx] : -1;
-        const int lx = px - (dx - 1) * (BS - 1), ly = py - (dy - 1) * (BS - 1);
-        PT[p] = slot >= 0 ? A.u[(size_t)slot * NP + lx + BS * ly] : __builtin_nan("");
-      }
-      __syncthreads();
-      // the children's values on the fine box, a quad of fine points (2X + {0, 1},
-      // 2Y + {0, 1}) per thread: the parent's value, its prediction along x, along y and
-      // along both, each as the refinement kernel's per-class tensor stencil forms it (the
-      // quad shares the parent values and the x-prediction of row Y)
-      int qlo[2], qhi[2], x0[2], nq[2];
-      for (int a = 0; a < 2; ++a) {
-        qlo[a] = r0[a] + cb[a] - E;
-        qhi[a] = qlo[a] + cnt[a] + 2 * E - 1;
-        x0[a] = qlo[a] >> 1;
-        nq[a] = (qhi[a] >> 1) - x0[a] + 1;
-      }
-      auto pt = [&](int X, int Y) { return PT[(X - plo[0]) + pw[0] * (Y - plo[1])]; };
-      auto put = [&](int qx, int qy, double v) {
-        const int i = G::idx(qx - qlo[0], qy - qlo[1], 0);
-        U[i] = v;
-        Ya[i] = stage_value(v);
-      };
-      auto row = [&](int X, int Y) { return P4(pt(X - 1, Y), pt(X, Y), pt(X + 1, Y), pt(X + 2, Y)); };
-      const float rnq = 1.0f / (float)nq[0];
-      for (int p = tid; p < nq[0] * nq[1]; p += blockDim.x) {
-        const int qy = fdiv(p, rnq);
-        const int X = x0[0] + p - qy * nq[0], Y = x0[1] + qy;
-        const bool ex = 2 * X >= qlo[0], ox = 2 * X + 1 <= qhi[0];
-        const bool ey = 2 * Y >= qlo[1], oy = 2 * Y + 1 <= qhi[1];
-        if (ex && ey) put(2 * X, 2 * Y, pt(X, Y));
-        if (ex && oy) put(2 * X, 2 * Y + 1, P4(pt(X, Y - 1), pt(X, Y), pt(X, Y + 1), pt(X, Y + 2)));
-        if (ox) {
-          const double ry = row(X, Y);
-          if (ey) put(2 * X + 1, 2 * Y, ry);
-          if (oy) put(2 * X + 1, 2 * Y + 1, P4(row(X, Y - 1), ry, row(X, Y + 1), row(X, Y + 2)));
-        }
-      }
-    } else {
-      // u over the region + E
-      const int nx = cnt[0] + 2 * E, ny = cnt[1] + 2 * E;
-      const float rnx = 1.0f / (float)nx;
-      for (int p = tid; p < nx * ny; p += blockDim.x) {
-        const int iy = fdiv(p, rnx), ix = p - iy * nx;
-        const int tx = r0[0] - E + ix, ty = r0[1] - E + iy;
-        const int dx = tx < 0 ? 0 : (tx > BS - 1 ? 2 : 1), dy = ty < 0 ? 0 : (ty > BS - 1 ? 2 : 1);
-        const int slot = tab[dy * 3 + dx];
-        const int lx = tx - (dx - 1) * (BS - 1), ly = ty - (dy - 1) * (BS - 1);
-        const double v = slot >= 0 ? A.u[(size_t)slot * NP + lx + BS * ly] : __builtin_nan("");
-        U[G::idx(ix, iy, 0)] = v;
-        Ya[G::idx(ix, iy, 0)] = stage_value(v);
+      if (s < 4) {
+        const KT ks = (KT)kv;
+        if (s == 1) k1[i] = ks;
+        if (s == 2) s23[i] = (double)ks;
+        if (s == 3) s23[i] = s23[i] + (double)ks;
+        const TT yn = stage_value(u[i] + A.alpha[s] * (double)ks);
+        if (act) Yn[q] = yn;
+      } else {
+        const double un = u[i] + A.h6 * (((double)k1[i] + (double)kv) + 2.0 * s23[i]);
+        if (ANA && act) U[q] = un;   // (in FP64 over the first array: this stage reads the second)
+        const int iy = q / TW, tx = r0[0] - E + q - iy * TW, ty = r0[1] - E + iy;
+        if (act && tx >= r0[0] && tx < r0[0] + cnt[0] && ty >= r0[1] && ty < r0[1] + cnt[1])
+          A.unew[(size_t)d.slot * NP + tx + BS * ty] = un;
       }
     }
     __syncthreads();
-    TT r;
-    if constexpr (sizeof(TT) == 8) r = A.lt.r[d.level];
-    else r = A.lt.rf[d.level];
-    TT* Y = Ya;
-    TT* Yn = Yb;
-    for (int s = 1; s <= 4; ++s) {
-      // k_s within E - s HW of the region, and in the same pass the next stage's values
-      // there; the last stage forms u_new (in place of u: a point's update reads only
-      // its own u) and stores it on the region
-      const int mr = E - HW * s;
-      const int nx = cnt[0] + 2 * mr, ny = cnt[1] + 2 * mr;
-      // row of the p-th point by a float reciprocal (p < 2^12, rows of at most 64
-      // points: exact, as in for_classes_2d)
-      const float rnx = 1.0f / (float)nx;
-      for (int p = tid; p < nx * ny; p += blockDim.x) {
-        const int qy = (int)(((float)p + 0.5f) * rnx);
-        const int ix = E - mr + (p - qy * nx), iy = E - mr + qy;
-        const int i[3] = {ix, iy, 0};
-        const int t[3] = {r0[0] - E + ix, r0[1] - E + iy, 0};
-        const int l[3] = {ix, iy, 0};
-        const int q = G::idx(ix, iy, 0);
-        const int kx = ix - (E - KO), ky = iy - (E - KO);
-        const bool kz = kx >= 0 && kx < cnt[0] + 2 * KO && ky >= 0 && ky < cnt[1] + 2 * KO;
-        const int kq = kx + KW * ky;
-        // (the swirl reads its LDS slices, the other kind is the constant velocity)
-        const TT kv = A.ph.kind == 1
-                          ? rhs_adv<2, BS, S, E, TT, TW, 1>(Y, i, t, d, r, A.ph, A.lt, A.cfac[s - 1], sw, l)
-                          : rhs_adv<2, BS, S, E, TT, TW, 2>(Y, i, t, d, r, A.ph, A.lt, A.cfac[s - 1], nullptr, l);
-        if (s < 4) {
-          const KT ks = (KT)kv;
-          if (kz) K[(s - 1) * KSZ + kq] = ks;
-          Yn[q] = stage_value(U[q] + A.alpha[s] * (double)ks);
-        } else {
-          const double k1 = (double)K[kq], k2 = (double)K[KSZ + kq], k3 = (double)K[2 * KSZ + kq];
-          const double k4 = (double)kv;
-          const double un = U[q] + A.h6 * ((k1 + k4) + 2.0 * (k2 + k3));
-          if (ANA) U[q] = un;
-          if (t[0] >= r0[0] && t[0] < r0[0] + cnt[0] && t[1] >= r0[1] && t[1] < r0[1] + cnt[1])
-            A.unew[(size_t)d.slot * NP + t[0] + BS * t[1]] = un;
-        }
-      }
-      __syncthreads();
-      TT* tmp = Y;
-      Y = Yn;
-      Yn = tmp;
-    }
-    if constexpr (ANA) {
-      // the analysis and the mothers' analysis read u_new only: one pass over both (no
-      // barrier between them), then one reduction for both maxima
-      double m[1] = {0.0};
-      TileDetails<BS, S, E> det{U, r0, m};
-      for_classes_2d<1>(det, r0, cnt);
-      double mm[1] = {sm >= 0 ? 0.0 : __builtin_nan("")};
-      if constexpr (MA) {
-        // second analysis of the speculated coarsening: this region's share of its
-        // mother's nodes; the host takes the maximum over the shares
-        if (sm >= 0) {
-          MotherDetails<BS, S, E> md;
-          md.U = U;
-          md.m = mm;
-          int m0[2], mn[2];
-          for (int a = 0; a < 2; ++a) {
-            md.off[a] = ((sm >> a) & 1) * (BS - 1);
-            md.r0[a] = r0[a];
-            // mother nodes whose child node lies in [r0, r0 + cnt)
-            const int lo = (r0[a] + md.off[a] + 1) >> 1, hi = (r0[a] + cnt[a] - 1 + md.off[a]) >> 1;
-            m0[a] = lo;
-            mn[a] = hi - lo + 1;
-          }
-          for_classes_2d<1>(md, m0, mn, (TPB - 384) & (TPB - 1));   // from thread 384 on
-        }
-      }
-      double vb = m[0], vm = mm[0];
-      wg_nanmax2<TPB>(vb, vm, red);
-      if (tid == 0) {
-        if constexpr (NSUBT > 1) {
-          A.part[(size_t)b * NSUBT + it.w % NSUBT] = vb;
-        } else {
-          A.maxd[b] = vb;
-          A.flags[b] = d.level > 1 && vb < A.thr ? (int8_t)-1 : (int8_t)0;
-        }
-        if constexpr (MA) A.mq[(size_t)b * NSUBT + it.w % NSUBT] = vm;
-      }
-      // speculated coarsening: the mother's nodes this block supplies (every node of a
-      // forest on one level is the block's own value); after the reduction, so that no
-      // barrier waits for these stores (the next work item rewrites u only after two
-      // barriers)
+  }
+  if constexpr (ANA) {
+    // the analysis and the mothers' analysis read u_new only: one pass over both (no
+    // barrier between them), then one reduction for both maxima
+    double m[1] = {0.0};
+    TileDetails<BS, S, E> det{U, r0, m};
+    for_classes_2d<1>(det, r0, cnt);
+    double mm[1] = {sm >= 0 ? 0.0 : __builtin_nan("")};
+    if constexpr (MA) {
+      // second analysis of the speculated coarsening: this region's share of its
+      // mother's nodes; the host takes the maximum over the shares
       if (sm >= 0) {
-        const int mch = sm & 7;
-        const size_t mbase = (size_t)(sm >> 3) * NP;
-        ParityClass<2> pc(0, r0, cnt);
-        for (int p = (tid + TPB - 576) & (TPB - 1); p < pc.total; p += TPB) {   // from thread 576 on
-          int t[3];
-          pc.coords(p, t);
-          bool skip = false;
-          int mnode = 0, mul = 1;
-          for (int a = 0; a < 2; ++a) {
-            const int bit = (mch >> a) & 1;
-            if (bit && t[a] == 0) skip = true;
-            mnode += (t[a] / 2 + bit * (BS - 1) / 2) * mul;
-            mul *= BS;
-          }
-          if (!skip) A.unew[mbase + mnode] = U[G::idx(t[0] - r0[0] + E, t[1] - r0[1] + E, 0)];
+        MotherDetails<BS, S, E> md;
+        md.U = U;
+        md.m = mm;
+        int m0[2], mn[2];
+        for (int a = 0; a < 2; ++a) {
+          md.off[a] = ((sm >> a) & 1) * (BS - 1);
+          md.r0[a] = r0[a];
+          // mother nodes whose child node lies in [r0, r0 + cnt)
+          const int lo = (r0[a] + md.off[a] + 1) >> 1, hi = (r0[a] + cnt[a] - 1 + md.off[a]) >> 1;
+          m0[a] = lo;
+          mn[a] = hi - lo + 1;
         }
+        for_classes_2d<1>(md, m0, mn, (TPB - 384) & (TPB - 1));   // from thread 384 on
+      }
+    }
+    double vb = m[0], vm = mm[0];
+    wg_nanmax2<TPB>(vb, vm, red);
+    if (tid == 0) {
+      if constexpr (NSUBT > 1) {
+        A.part[(size_t)b * NSUBT + it.w % NSUBT] = vb;
+      } else {
+        A.maxd[b] = vb;
+        A.flags[b] = d.level > 1 && vb < A.thr ? (int8_t)-1 : (int8_t)0;
+      }
+      if constexpr (MA) A.mq[(size_t)b * NSUBT + it.w % NSUBT] = vm;
+    }
+    // speculated coarsening: the mother's nodes this block supplies (every node of a
+    // forest on one level is the block's own value); after the reduction, so that no
+    // barrier waits for these stores
+    if (sm >= 0) {
+      const int mch = sm & 7;
+      const size_t mbase = (size_t)(sm >> 3) * NP;
+      ParityClass<2> pc(0, r0, cnt);
+      for (int p = (tid + TPB - 576) & (TPB - 1); p < pc.total; p += TPB) {   // from thread 576 on
+        int t[3];
+        pc.coords(p, t);
+        bool skip = false;
+        int mnode = 0, mul = 1;
+        for (int a = 0; a < 2; ++a) {
+          const int bit = (mch >> a) & 1;
+          if (bit && t[a] == 0) skip = true;
+          mnode += (t[a] / 2 + bit * (BS - 1) / 2) * mul;
+          mul *= BS;
+        }
+        if (!skip) A.unew[mbase + mnode] = U[G::idx(t[0] - r0[0] + E, t[1] - r0[1] + E, 0)];
       }
     }
   }
@@ -1899,7 +1942,7 @@ template <int B, int NS, typename TT, typename KT>
 static hipError_t rk4t_go(bool ana, bool ref, bool ma, int tpb, int grid, const Rk4tArgs& a, hipStream_t st) {
   if (ma) {
     if (!ana || !ref) return hipErrorInvalidValue;
-    const size_t lds = TileGeo<B, NS, true, true>::template lds<TT, KT>();
+    const size_t lds = TileGeo<B, NS, true, true>::template lds<TT>();
     if (tpb == 256) return go(k_rk4t<B, NS, TT, KT, true, 256, true, true>, grid, lds, st, a, 256);
     if constexpr (NS <= 2) {
       if (tpb == 512) return go(k_rk4t<B, NS, TT, KT, true, 512, true, true>, grid, lds, st, a, 512);
@@ -1908,7 +1951,7 @@ static hipError_t rk4t_go(bool ana, bool ref, bool ma, int tpb, int grid, const 
     return hipErrorInvalidValue;
   }
   if (ana) {
-    const size_t lds = TileGeo<B, NS, true>::template lds<TT, KT>();
+    const size_t lds = TileGeo<B, NS, true>::template lds<TT>();
     if (ref) {
       if (tpb == 256) return go(k_rk4t<B, NS, TT, KT, true, 256, true>, grid, lds, st, a, 256);
       if constexpr (NS <= 2) {
@@ -1926,12 +1969,15 @@ static hipError_t rk4t_go(bool ana, bool ref, bool ma, int tpb, int grid, const 
   }
   if (ref) return hipErrorInvalidValue;
   if (tpb != 256) return hipErrorInvalidValue;
-  return go(k_rk4t<B, NS, TT, KT, false, 256>, grid, TileGeo<B, NS, false>::template lds<TT, KT>(), st, a);
+  // (threads of the plain step: about five tile points each)
+  constexpr int T = B == 33 && NS == 1 ? 512 : 256;
+  return go(k_rk4t<B, NS, TT, KT, false, T>, grid, TileGeo<B, NS, false>::template lds<TT>(), st, a, T);
 }
 
 hipError_t launch_rk4t(const Shape& s, int precision, int nsub, bool analysis, bool refine, bool mothers, int tpb,
-                       int grid, const Rk4tArgs& a, hipStream_t st) {
+                       const Rk4tArgs& a, hipStream_t st) {
   if (s.dim != 2 || s.hw != 2 || s.nf != 1) return hipErrorInvalidValue;
+  const int grid = a.topo.h.n_blocks * nsub * nsub;   // one workgroup per work item
 #define X(B, P, NS)                                                                                              \
   if (s.bs == B && precision == P && nsub == NS) {                                                              \
     if constexpr (P == 0) return rk4t_go<B, NS, double, double>(analysis, refine, mothers, tpb, grid, a, st);   \

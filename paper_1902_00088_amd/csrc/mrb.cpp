@@ -1023,7 +1023,6 @@ Rk4tArgs rk4t_args(mrb_ctx* c, double t, double dt) {
 // u_new folded in or not
 mrb_status launch_tiled(mrb_ctx* c, int tn, const Rk4tArgs& ra, bool analysis, int tpb = 256, bool refine = false,
                         bool mothers = false) {
-  const long work = (long)nblk(c) * tn * tn;
   // algorithmic bytes of the work the launch performs, counted as for the stage,
   // analysis and refinement launches it replaces (an RK4 step: the four stages' bytes
   // per node; the analysis: 8 per node; the refinement: 8 (1 + 2^d) per parent node).
@@ -1042,8 +1041,7 @@ mrb_status launch_tiled(mrb_ctx* c, int tn, const Rk4tArgs& ra, bool analysis, i
     c->part_st.level = c->leaves.empty() ? 0 : c->leaves[0].level;
   }
   TimeScope rs(c, T_RK4T, bytes);
-  HIPCHK(c, launch_rk4t(c->shape, c->cfg.precision, tn, analysis, refine, mothers, tpb, grid_for(c, work), ra,
-                        c->stream));
+  HIPCHK(c, launch_rk4t(c->shape, c->cfg.precision, tn, analysis, refine, mothers, tpb, ra, c->stream));
   return MRB_OK;
 }
 
