@@ -252,30 +252,35 @@ struct DevTopoArgs {
   TopoHeader old_h;
   char* new_base;
   TopoHeader new_h;
-  int* cells;                       // dense index: position in the current grid, or -1
+  int* cells;                       // dense index: pool slot of the leaf of a cell, or -1
   int cell_off[kMaxLevels + 1];     // first cell of each level
   int* free_stack;
   int free_top;                     // entries in the free stack at launch
   const int8_t* flags;              // analysis flags of the current grid (coarsening plan)
   const double* maxd;               // and its detail maxima [n][nf] (checked for finiteness)
   int nf;
-  int* scratch;                     // [3 * max_blocks] ints
-  int* edges;                       // [2 + 2 * max_blocks * entry stride] ints (coarsening plan;
-                                    // first the candidates, then the edges)
+  int* fam;                         // [max_blocks] by slot: candidate family, or -1 (coarsening);
+                                    // by parent: its block of the grid before (refinement)
+  int* dead;                        // [max_blocks] by position: 0 at the first member of a live family
+  unsigned long long* live;         // [max_blocks / 64 + 4] bits by position: dead == 0
+  unsigned char* isp;               // [max_blocks + 64] by position: 1 below jmax (kept by k_entries)
+  int* edges;                       // [2 + 2 * max_blocks * entry stride] ints: edge count, any
+                                    // candidates (both zero between plans), edges
   int* err;                         // device word: error bits (1 not graded, 2 non-finite detail
                                     // norm; the coarsening plan adds 4: too few free slots)
-  int* out;                         // mapped host ints (plain stores only): [0] parents or families,
-                                    // [1] new block count, [2] new free-stack top, [3] error bits
-                                    // (the coarsening plan moves and clears *err), [4..) level histogram
+  int* out;                         // mapped host ints (plain stores only), written by the coarsening
+                                    // plan: [0] families, [1] new block count, [2] new free-stack top,
+                                    // [3] error bits (moves and clears *err), [4..) families per level
   int dim, bs, jmax, nch;
 };
 hipError_t launch_plan_refine(const DevTopoArgs& a, hipStream_t st);
-hipError_t launch_plan_coarsen(const DevTopoArgs& a, int grid, hipStream_t st);   // four launches
-hipError_t launch_index(const DevTopoArgs& a, int set, int grid, hipStream_t st);   // set 0: clear old, 1: set new
-hipError_t launch_entries(const DevTopoArgs& a, int grid, hipStream_t st);
+hipError_t launch_plan_coarsen(const DevTopoArgs& a, hipStream_t st);    // three launches
+hipError_t launch_coarsen_apply(const DevTopoArgs& a, hipStream_t st);   // new_h.n_fam families merge
+hipError_t launch_index(const DevTopoArgs& a, hipStream_t st);           // of a grid the host has sent
+hipError_t launch_entries(const DevTopoArgs& a, hipStream_t st);
 hipError_t launch_fill_int(int* p, size_t n, int v, hipStream_t st);
 constexpr int kDevOutInts = 4 + kMaxLevels;
-constexpr int kAliveLds = 32768;   // families whose live flags the coarsening plan keeps in LDS
+constexpr int kAliveLds = 32768;   // blocks whose live flags the coarsening plan keeps in LDS
 
 // Library-owned device scratch of kScratchBytes per GPU (a static device array, no
 // allocation): scratch_setup stores its address on the current device in *out.

@@ -345,8 +345,8 @@ struct mrb_ctx {
     size_t ncells = 0;
     int cell_off[kMaxLevels + 1];
     int* stack = nullptr;        // free pool slots
-    int* scratch = nullptr;      // [3 * max_blocks]
-    int* edges = nullptr;        // coarsening plan: edge count, family count, edges
+    char* scratch = nullptr;     // family, live and parent flags (DevTopoArgs)
+    int* edges = nullptr;        // coarsening plan: edge count, any candidates, edges
     int* err = nullptr;          // device error word
     int8_t* flags = nullptr;     // analysis flags and maxima of the device path
     double* maxd = nullptr;
@@ -2111,6 +2111,27 @@ TopoHeader dev_header(const mrb_ctx* c, int n, int nref, int nfam) {
   return h;
 }
 
+// the flag arrays of the topology kernels in one allocation; returns its bytes
+size_t dev_scratch(size_t mb, char* base, DevTopoArgs* a) {
+  size_t off = 0;
+  auto place = [&](size_t bytes) -> char* {
+    char* p = base + off;
+    off = align16(off + bytes);
+    return p;
+  };
+  char* fam = place(mb * sizeof(int));
+  char* dead = place(mb * sizeof(int));
+  char* live = place((mb / 64 + 4) * sizeof(unsigned long long));
+  char* isp = place(mb + 64);
+  if (a) {
+    a->fam = (int*)fam;
+    a->dead = (int*)dead;
+    a->live = (unsigned long long*)live;
+    a->isp = (unsigned char*)isp;
+  }
+  return off;
+}
+
 // allocate the device path's buffers once; false (with dev.unavailable) if the dense
 // index of every possible block would not fit
 mrb_status dev_alloc(mrb_ctx* c) {
@@ -2136,10 +2157,11 @@ mrb_status dev_alloc(mrb_ctx* c) {
   HIPCHK(c, hipMalloc((void**)&D.arena[1], ab));
   HIPCHK(c, hipMalloc((void**)&D.cells, cells * sizeof(int)));
   HIPCHK(c, hipMalloc((void**)&D.stack, mb * sizeof(int)));
-  HIPCHK(c, hipMalloc((void**)&D.scratch, 3 * mb * sizeof(int)));
+  HIPCHK(c, hipMalloc((void**)&D.scratch, dev_scratch(mb, nullptr, nullptr)));
   HIPCHK(c, hipMalloc((void**)&D.edges, (2 + 2 * mb * (size_t)D.stride) * sizeof(int)));
   HIPCHK(c, hipMalloc((void**)&D.err, 256));
   HIPCHK(c, hipMemset(D.err, 0, 256));
+  HIPCHK(c, launch_fill_int(D.edges, 2, 0, c->stream));
   HIPCHK(c, hipMalloc((void**)&D.flags, std::max(mb, (size_t)256)));
   HIPCHK(c, hipMalloc((void**)&D.maxd, std::max(mb * c->cfg.nfields * sizeof(double), (size_t)256)));
   HIPCHK(c, hipHostMalloc((void**)&D.h_out, kDevOutInts * sizeof(int), hipHostMallocMapped | hipHostMallocCoherent));
@@ -2174,7 +2196,7 @@ DevTopoArgs dev_args(mrb_ctx* c, int from, const TopoHeader& oh, int to, const T
   a.flags = D.flags;
   a.maxd = D.maxd;
   a.nf = c->cfg.nfields;
-  a.scratch = D.scratch;
+  dev_scratch((size_t)c->cfg.max_blocks, D.scratch, &a);
   a.edges = D.edges;
   a.err = D.err;
   a.out = D.d_out;
@@ -2184,8 +2206,6 @@ DevTopoArgs dev_args(mrb_ctx* c, int from, const TopoHeader& oh, int to, const T
   a.nch = 1 << c->cfg.dim;
   return a;
 }
-
-int dev_grid(long waves) { return (int)std::max(1L, std::min(8192L, (waves + 3) / 4)); }
 
 // the device takes over the host forest: descriptors and free stack uploaded, dense
 // index and entries built on the device
@@ -2216,8 +2236,8 @@ mrb_status dev_push(mrb_ctx* c) {
   DevTopoArgs a = dev_args(c, D.cur, h, D.cur, h);
   {
     TimeScope ts(c, T_TOPO, 0.0);
-    HIPCHK(c, launch_index(a, 1, dev_grid(4L * n), c->stream));
-    HIPCHK(c, launch_entries(a, dev_grid(n), c->stream));
+    HIPCHK(c, launch_index(a, c->stream));
+    HIPCHK(c, launch_entries(a, c->stream));
   }
   c->arena = D.arena[D.cur];
   c->arena_hdr = h;
@@ -2287,9 +2307,7 @@ mrb_status dev_refine_all(mrb_ctx* c) {
   {
     TimeScope ts(c, T_TOPO, 0.0);
     HIPCHK(c, launch_plan_refine(a, c->stream));
-    HIPCHK(c, launch_index(a, 0, dev_grid(4L * D.n), c->stream));
-    HIPCHK(c, launch_index(a, 1, dev_grid(4L * nnew), c->stream));
-    HIPCHK(c, launch_entries(a, dev_grid((long)nnew + nref), c->stream));
+    HIPCHK(c, launch_entries(a, c->stream));
   }
   long h2[kMaxLevels] = {0};
   for (int l = 1; l < kMaxLevels; ++l) {
@@ -2334,7 +2352,7 @@ mrb_status dev_adapt(mrb_ctx* c, int* npass) {
     DevTopoArgs a = dev_args(c, D.cur, c->arena_hdr, nxt, dev_header(c, 0, 0, 0));
     {
       TimeScope ts(c, T_TOPO, 0.0);
-      HIPCHK(c, launch_plan_coarsen(a, dev_grid((long)D.n * D.stride / 16), c->stream));
+      HIPCHK(c, launch_plan_coarsen(a, c->stream));
     }
     {
       HostTimer ht(&c->hus_wait);
@@ -2354,11 +2372,13 @@ mrb_status dev_adapt(mrb_ctx* c, int* npass) {
     a = dev_args(c, D.cur, c->arena_hdr, nxt, nh);
     {
       TimeScope ts(c, T_TOPO, 0.0);
-      HIPCHK(c, launch_index(a, 0, dev_grid(4L * D.n), c->stream));
-      HIPCHK(c, launch_index(a, 1, dev_grid(4L * nnew), c->stream));
-      HIPCHK(c, launch_entries(a, dev_grid(nnew), c->stream));
+      HIPCHK(c, launch_coarsen_apply(a, c->stream));
+      HIPCHK(c, launch_entries(a, c->stream));
     }
-    for (int l = 0; l < kMaxLevels; ++l) D.hist[l] = D.h_out[4 + l];
+    for (int l = 1; l < kMaxLevels; ++l) {
+      D.hist[l] -= (long)D.h_out[4 + l] * nch;
+      D.hist[l - 1] += D.h_out[4 + l];
+    }
     D.top = top;
     D.n = nnew;
     D.cur = nxt;

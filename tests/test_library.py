@@ -1170,3 +1170,45 @@ def test_2d_zone_kernels_on_ragged_forests(which, seed, p_refine):
         mixed.append(s.read_blocks())
         s.close()
     assert np.array_equal(mixed[0], mixed[1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", ["2d", "3d", "wide"])
+def test_device_topology_on_ragged_and_wide_grids(case):
+    """Plans made on the device equal the host's, slots' values and flags included, on random
+    graded forests of three levels with rough blocks scattered over them (families that merge,
+    families kept by a finer neighbour) and on a grid of 40,960 blocks after the refinement,
+    more than the coarsening plan holds flags of in LDS."""
+    if case == "3d":
+        cfg = W.C4(jmax=4, eps=1e-2, max_blocks=9000)
+        lv, co = W.random_graded_forest(3, 3, 1, 0.3)
+    elif case == "2d":
+        cfg = W.C2(jmax=6, eps=1e-2, form=W.FORM_FUSED, max_blocks=5000)
+        lv, co = W.random_graded_forest(2, 5, 3, 0.4)
+    else:
+        cfg = W.C1(jmax=8, eps=1e-2, form=W.FORM_FUSED).replace(max_blocks=55000)
+        lv, co = W.uniform_forest(cfg, 6)
+        fine = co[:, 0] % 8 < 4
+        kids = np.concatenate([2 * co[fine] + np.array([i, j] + [0] * (co.shape[1] - 2)) for i in (0, 1) for j in (0, 1)])
+        lv = np.concatenate([lv[~fine], np.full(len(kids), 7, lv.dtype)])
+        co = np.concatenate([co[~fine], kids.astype(co.dtype)])
+    cfg = cfg.replace(dt=cfg.dt * 2.0 ** -6)
+    out = []
+    for mode in (0, 1):
+        s = M.Solver(cfg)
+        s.init_forest(lv, co)
+        data = W.sample(cfg, *s.read_forest())
+        rng = np.random.default_rng(11)
+        rough = rng.random(len(data)) < 0.02
+        data[rough] += 0.05 * rng.standard_normal(data[rough].shape)
+        s.load_blocks(data)
+        s.set_graph(0)
+        s.set_topology(mode)
+        for k in range(2):
+            s.step(k * cfg.dt, cfg.dt)
+            assert s.stats()["topology"] == ("device" if mode else "host")
+        out.append((*s.read_forest(), s.read_blocks(), *s.get_flags()))
+        s.close()
+    assert 4 < len(out[0][0]) < 40000 and len(set(out[0][0].tolist())) > 1
+    for a, b in zip(*out):
+        assert np.array_equal(_bits(a) if a.dtype == np.float64 else a, _bits(b) if b.dtype == np.float64 else b)
