@@ -221,6 +221,8 @@ constexpr int kColumnThreads = 448;
 hipError_t launch_stage3(int precision, const StageArgs& a, hipStream_t st);
 hipError_t launch_mr3(const MrArgs& a, hipStream_t st);
 hipError_t launch_refine3(const RefineArgs& a, hipStream_t st);
+hipError_t launch_mr2(const Shape& s, int tpb, const MrArgs& a, hipStream_t st);
+hipError_t launch_refine2(const Shape& s, const RefineArgs& a, hipStream_t st);
 // 2D stages of whole blocks (halves of them for Navier-Stokes) and the filter (plane2.hip):
 // the stage variant of plane_threads threads
 constexpr int kNsThreads = 576;
@@ -240,8 +242,8 @@ hipError_t launch_rk4t(const Shape& s, int precision, int nsub, bool analysis, b
                        const Rk4tArgs& a, hipStream_t st);
 int rk4t_variants(const Shape& s, int precision, int* nsub, int cap);
 hipError_t launch_mr(const Shape& s, int nsub, int tpb, int grid, const MrArgs& a, hipStream_t st);
-int mr_threads(const Shape& s, int nsub, int* tpb, int cap);   // compiled workgroup sizes (256 first)
-hipError_t launch_refine(const Shape& s, int nsub, int grid, const RefineArgs& a, hipStream_t st);
+int mr_threads(const Shape& s, int nsub, int* tpb, int cap);   // workgroup sizes to ask for (256, the default, first)
+hipError_t launch_refine(const Shape& s, const RefineArgs& a, hipStream_t st);
 hipError_t launch_coarsen(const Shape& s, int grid, const CoarsenArgs& a, hipStream_t st);
 hipError_t launch_read(const Shape& s, int grid, const ReadArgs& a, hipStream_t st);
 hipError_t launch_scatter(const double* src, const int* slots, int n, size_t bsz, double* dst, hipStream_t st);
@@ -293,7 +295,7 @@ bool shape_supported(const Shape& s);
 int stage_variants(const Shape& s, int precision, int* nsub, int cap);
 // threads-per-workgroup choices compiled for a stage tiling (256 always among them)
 int stage_threads(const Shape& s, int precision, int nsub, int* tpb, int cap);
-// sub-tile counts of the analysis (kind 0) and refinement (kind 1) kernels
-int aux_variants(const Shape& s, int kind, int* nsub, int cap);
+// sub-tile counts of the analysis kernels (1 first)
+int aux_variants(const Shape& s, int* nsub, int cap);
 
 }  // namespace mrb

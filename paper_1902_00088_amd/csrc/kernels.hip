@@ -1393,72 +1393,6 @@ __global__ void __launch_bounds__(256) k_rhs_plain(StageArgs A) {
   }
 }
 
-// child nodes of one parity class (see k_refine).  fm[a][i]: finer entries whose region
-// holds fine coordinate Q = cb + q0 + i along axis a (null when the parent has no finer
-// neighbour); the first such entry in list order supplies a node they hold.
-template <int DIM, int BS, int S, int H, int NF, int SQ>
-struct RefineBody {
-  using G = Geo<DIM, BS, S, H>;
-  const double* tile;
-  const NbEntry* ent;
-  const unsigned long long (*fm)[SQ];
-  const int* q0;
-  const int* qn;
-  const int* r0;
-  const int* cb;
-  size_t cbase;
-  double* u;
-  __device__ __forceinline__ RefineBody(const double* t_, const NbEntry* e_, const unsigned long long (*fm_)[SQ],
-                                        const int* q0_, const int* qn_, const int* r0_, const int* cb_, size_t cb0,
-                                        double* u_)
-      : tile(t_), ent(e_), fm(fm_), q0(q0_), qn(qn_), r0(r0_), cb(cb_), cbase(cb0), u(u_) {}
-  template <int NX, int NY, int NZ>
-  __device__ __forceinline__ void go(int cls) {
-    ParityClass<DIM> pc(cls, q0, qn);
-    for (int p = threadIdx.x; p < pc.total; p += blockDim.x) {
-      int qq[3];
-      pc.coords(p, qq);
-      int Q[3] = {0, 0, 0};
-      bool bnd = false;
-      int q = 0, mulq = 1;
-      for (int a = 0; a < DIM; ++a) {
-        q += qq[a] * mulq;
-        mulq *= BS;
-        Q[a] = qq[a] + cb[a];
-        if (Q[a] == 0 || Q[a] == 2 * (BS - 1)) bnd = true;
-      }
-      if (cls != 0 && bnd && fm) {
-        unsigned long long cand = ~0ull;
-        for (int a = 0; a < DIM; ++a) cand &= fm[a][qq[a] - q0[a]];
-        if (cand) {
-          const NbEntry& E = ent[__ffsll((long long)cand) - 1];
-          int s = 0, mul = 1;
-          for (int a = 0; a < DIM; ++a) {
-            s += (Q[a] - 2 * E.o[a]) * mul;
-            mul *= BS;
-          }
-#pragma unroll
-          for (int f = 0; f < NF; ++f) u[cbase + (size_t)f * NP + q] = u[((size_t)E.slot * NF + f) * NP + s];
-          continue;
-        }
-      }
-      // parent coordinate -> region-local -> tile coordinate
-      const int bb[3] = {NX == 4 ? (Q[0] - 3) / 2 - r0[0] + H : Q[0] / 2 - r0[0] + H,
-                         NY == 4 ? (Q[1] - 3) / 2 - r0[1] + H : Q[1] / 2 - r0[1] + H,
-                         DIM > 2 ? (NZ == 4 ? (Q[2] - 3) / 2 - r0[2] + H : Q[2] / 2 - r0[2] + H) : 0};
-      const int stride[3] = {1, 1, 1};
-#pragma unroll
-      for (int f = 0; f < NF; ++f) {
-        const double* T = tile + f * TSZ;
-        auto at = [&](int x, int y, int z) { return T[G::idx(x, y, z)]; };
-        u[cbase + (size_t)f * NP + q] = tensor_fixed<NX, NY, NZ, double>(at, bb, stride);
-      }
-    }
-  }
-  static constexpr int TSZ = Geo<DIM, BS, S, H>::TSZ;
-  static constexpr int NP = Geo<DIM, BS, S, H>::NP;
-};
-
 // ---------------------------------------------------------------------------
 // multiresolution analysis: details d = u - P(R(u)), per-field max, flag;
 // redundant nodes owned by finer neighbours are written back to the pool
@@ -1501,8 +1435,11 @@ struct DetailsBodyC {
   }
 };
 
-template <int DIM, int BS, int NF, int NSUB, int TPB = 256>
-__global__ void __launch_bounds__(TPB) k_mr(MrArgs A) {
+// (sub-tiles only: whole blocks are analysed by k_mr2 and k_mr3)
+template <int DIM, int BS, int NF, int NSUB>
+__global__ void __launch_bounds__(256) k_mr(MrArgs A) {
+  static_assert(NSUB > 1, "sub-tiles");
+  constexpr int TPB = 256;
   // the region's nodes in the tile; the even nodes up to H = 3 around it (a region may
   // start at an odd node, whose coarse stencil reaches 3 back) in the coarse array
   constexpr int S = (BS + NSUB - 1) / NSUB, H = 3;
@@ -1568,21 +1505,15 @@ __global__ void __launch_bounds__(TPB) k_mr(MrArgs A) {
         v[f] = red[0][f];
         for (int q = 1; q < (int)(blockDim.x >> 6); ++q) v[f] = nanmax(v[f], red[q][f]);
       }
-      bool last = true;
-      if constexpr (NSUBT > 1) {
-        // combine sub-tiles: |d| >= 0 (or NaN, whose bit pattern is larger than +Inf), so
-        // the unsigned maximum of the bit patterns is the maximum; the last sub-tile to
-        // finish reads and clears the partials
-        for (int f = 0; f < NF; ++f) atomicMax(&A.acc[(size_t)b * NF + f], (unsigned long long)__double_as_longlong(v[f]));
+      // combine sub-tiles: |d| >= 0 (or NaN, whose bit pattern is larger than +Inf), so
+      // the unsigned maximum of the bit patterns is the maximum; the last sub-tile to
+      // finish reads and clears the partials
+      for (int f = 0; f < NF; ++f) atomicMax(&A.acc[(size_t)b * NF + f], (unsigned long long)__double_as_longlong(v[f]));
+      __threadfence();
+      if (atomicAdd(&A.done[b], 1) == NSUBT - 1) {
         __threadfence();
-        last = atomicAdd(&A.done[b], 1) == NSUBT - 1;
-        if (last) {
-          __threadfence();
-          for (int f = 0; f < NF; ++f) v[f] = __longlong_as_double((long long)atomicExch(&A.acc[(size_t)b * NF + f], 0ull));
-          atomicExch(&A.done[b], 0);
-        }
-      }
-      if (last) {
+        for (int f = 0; f < NF; ++f) v[f] = __longlong_as_double((long long)atomicExch(&A.acc[(size_t)b * NF + f], 0ull));
+        atomicExch(&A.done[b], 0);
         bool coarse = d.level > 1;
         for (int f = 0; f < NF; ++f) {
           A.maxd[(size_t)b * NF + f] = v[f];
@@ -1624,79 +1555,6 @@ __global__ void __launch_bounds__(TPB) k_mr(MrArgs A) {
           A.u[mbase + (size_t)f * NP + mnode] = from_tile ? tile[f * TSZ + ti] : A.u[base + (size_t)f * NP + node];
       }
     }
-    __syncthreads();
-  }
-}
-
-// ---------------------------------------------------------------------------
-// refinement, one workgroup per (parent, child, sub-tile of the child): the
-// child's nodes take the synchronised value at level l+1 -- a finer neighbour's
-// stored value where one holds the node, else the parent's value (even nodes)
-// or its prediction (odd nodes)
-// ---------------------------------------------------------------------------
-template <int DIM, int BS, int NF, int NSUB>
-__global__ void __launch_bounds__(256) k_refine(RefineArgs A) {
-  constexpr int SQ = (BS + NSUB - 1) / NSUB;       // child nodes per axis and sub-tile
-  constexpr int HWR = 2, H = HWR + 3, S = SQ / 2 + 2;
-  using SG = SGeo<DIM, BS, S, HWR>;
-  constexpr int NP = SG::NP, NCH = 1 << DIM;
-  constexpr int NSUBT = Pow<DIM, NSUB>::v;
-  __shared__ GState<DIM, S + 2 * H> g;
-  __shared__ SEnt se[kMaxEnt];
-  __shared__ unsigned long long fm[DIM][SQ];
-  extern __shared__ __align__(16) char smem[];
-  double* tile = reinterpret_cast<double*>(smem);
-  double* carr = tile + NF * SG::TSZ;
-  const int nref = A.topo.h.n_ref;
-  for (XcdWork it(nref * NCH * NSUBT); it.ok(); it.next()) {
-    const int w = it.w;
-    const int ri = w / (NCH * NSUBT), ch = (w / NSUBT) % NCH;
-    const RefineDesc R = A.topo.ref()[ri];
-    const BlockDesc d = A.topo.pblk()[ri];
-    int q0[3], qn[3];
-    subregion<DIM>(w % NSUBT, NSUB, SQ, BS, q0, qn);
-    // parent region holding the sub-tile's fine nodes Q = cb (bs-1) + q (parent coords Q/2)
-    int r0[3] = {0, 0, 0}, cnt[3] = {1, 1, 1};
-    for (int a = 0; a < DIM; ++a) {
-      const int off = ((ch >> a) & 1) * (BS - 1);
-      r0[a] = (off + q0[a]) >> 1;
-      cnt[a] = ((off + q0[a] + qn[a]) >> 1) - r0[a] + 1;
-    }
-    gsetup<DIM, BS, S, H>(g, d, A.topo.pnb(ri), A.topo.h.pnb_stride, r0);
-    sent_setup<DIM, BS, NF>(se, g.ent, d.n_ent);
-    __syncthreads();
-    YSrc<double, double, false> src{A.u, nullptr, 0.0, nullptr};
-    if (d.n_coarse > 0) {
-      sgather<DIM, BS, S, HWR, NF, true, double>(tile, carr, g, se, d.slot, r0, cnt, src);
-      spredict<DIM, BS, S, HWR, NF, double>(tile, carr, g, r0, cnt);
-    } else {
-      sgather<DIM, BS, S, HWR, NF, false, double>(tile, carr, g, se, d.slot, r0, cnt, src);
-    }
-    const size_t cbase = (size_t)R.child[ch] * NF * NP;
-    int cb[3] = {0, 0, 0};
-    for (int a = 0; a < DIM; ++a) cb[a] = ((ch >> a) & 1) * (BS - 1);
-    // finer entries come last in the list: the lookup table is needed only if the last
-    // entry is finer (a uniform branch)
-    const bool has_fine = d.n_ent > 0 && g.ent[d.n_ent - 1].dl > 0;
-    if (has_fine) {
-      for (int k = threadIdx.x; k < DIM * SQ; k += blockDim.x) {
-        const int a = k / SQ, i = k % SQ;
-        const int Q = cb[a] + q0[a] + i;
-        unsigned long long mm = 0;
-        for (int e = 0; e < d.n_ent; ++e) {
-          const int l = Q - 2 * g.ent[e].o[a];
-          if (g.ent[e].dl > 0 && l >= 0 && l <= BS - 1) mm |= 1ull << e;
-        }
-        fm[a][i] = mm;
-      }
-      __syncthreads();
-    }
-    // one parity class of child nodes at a time (fine parity = parity of q, since
-    // bs-1 is even): even nodes copy the parent, odd ones are predicted, and nodes on
-    // the parent's boundary held by a finer neighbour take that neighbour's value
-    RefineBody<DIM, BS, S, HWR, NF, SQ> rf(tile, g.ent, has_fine ? fm : nullptr, q0, qn, r0, cb, cbase, A.u);
-    rf.template go<1, 1, 1>(0);
-    for_odd_classes<DIM>(rf);
     __syncthreads();
   }
 }
@@ -2027,7 +1885,7 @@ hipError_t launch_plain(const Shape& s, int grid, const StageArgs& a, hipStream_
   return hipErrorInvalidValue;
 }
 
-// analysis (kind 0) and refinement (kind 1) tilings per shape
+// analysis tilings per shape
 #define MRB_AUX_VARIANTS(X) \
   X(2, 17, 2, 1, 1)         \
   X(2, 17, 2, 1, 2)         \
@@ -2039,21 +1897,12 @@ hipError_t launch_plain(const Shape& s, int grid, const StageArgs& a, hipStream_
   X(3, 17, 2, 1, 1)         \
   X(3, 17, 2, 1, 2)
 
-int aux_variants(const Shape& s, int kind, int* nsub, int cap) {
+int aux_variants(const Shape& s, int* nsub, int cap) {
   int n = 0;
-  (void)kind;
 #define X(D, B, W, F, NS) if (s.dim == D && s.bs == B && s.hw == W && s.nf == F && n < cap) nsub[n++] = NS;
   MRB_AUX_VARIANTS(X)
 #undef X
   return n;
-}
-
-template <int D, int B, int F, int NS, int T = 256>
-static hipError_t mr_go(int grid, const MrArgs& a, hipStream_t st) {
-  if constexpr (D == 3 && NS == 1) return launch_mr3(a, st);   // whole 3D blocks: a column per thread
-  constexpr int S = (B + NS - 1) / NS;
-  using SG = SGeo<D, B, S, 0>;
-  return go(k_mr<D, B, F, NS, T>, grid, sizeof(double) * F * (SG::TSZ + SG::CSZ), st, a, T);
 }
 
 // the analysis of whole 2D blocks with larger workgroups (a small forest leaves most
@@ -2075,21 +1924,17 @@ int mr_threads(const Shape& s, int nsub, int* tpb, int cap) {
 }
 
 template <int D, int B, int F, int NS>
-static hipError_t refine_go(int grid, const RefineArgs& a, hipStream_t st) {
-  if constexpr (D == 3 && NS == 1) return launch_refine3(a, st);
-  constexpr int SQ = (B + NS - 1) / NS;
-  using SG = SGeo<D, B, SQ / 2 + 2, 2>;
-  return go(k_refine<D, B, F, NS>, grid, sizeof(double) * F * (SG::TSZ + SG::CSZ), st, a);
+static hipError_t mr_go(int grid, const MrArgs& a, hipStream_t st) {
+  if constexpr (NS > 1) {
+    using SG = SGeo<D, B, (B + NS - 1) / NS, 0>;
+    return go(k_mr<D, B, F, NS>, grid, sizeof(double) * F * (SG::TSZ + SG::CSZ), st, a);
+  }
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_mr(const Shape& s, int nsub, int tpb, int grid, const MrArgs& a, hipStream_t st) {
-  if (tpb != 256) {
-#define X(D, B, W, F, T) \
-    if (s.dim == D && s.bs == B && s.hw == W && s.nf == F && nsub == 1 && tpb == T) return mr_go<D, B, F, 1, T>(grid, a, st);
-    MRB_MR_WIDE(X)
-#undef X
-    return hipErrorInvalidValue;
-  }
+  if (nsub == 1) return s.dim == 2 ? launch_mr2(s, tpb, a, st) : tpb == 256 ? launch_mr3(a, st) : hipErrorInvalidValue;
+  if (tpb != 256) return hipErrorInvalidValue;
 #define X(D, B, W, F, NS) \
   if (s.dim == D && s.bs == B && s.hw == W && s.nf == F && nsub == NS) return mr_go<D, B, F, NS>(grid, a, st);
   MRB_AUX_VARIANTS(X)
@@ -2097,12 +1942,8 @@ hipError_t launch_mr(const Shape& s, int nsub, int tpb, int grid, const MrArgs& 
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_refine(const Shape& s, int nsub, int grid, const RefineArgs& a, hipStream_t st) {
-#define X(D, B, W, F, NS) \
-  if (s.dim == D && s.bs == B && s.hw == W && s.nf == F && nsub == NS) return refine_go<D, B, F, NS>(grid, a, st);
-  MRB_AUX_VARIANTS(X)
-#undef X
-  return hipErrorInvalidValue;
+hipError_t launch_refine(const Shape& s, const RefineArgs& a, hipStream_t st) {
+  return s.dim == 2 ? launch_refine2(s, a, st) : launch_refine3(a, st);
 }
 
 hipError_t launch_coarsen(const Shape& s, int grid, const CoarsenArgs& a, hipStream_t st) {

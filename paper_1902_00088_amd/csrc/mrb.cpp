@@ -292,7 +292,6 @@ struct mrb_ctx {
   int tpb = 256;               // stage threads per workgroup (for the tuned nsub)
   int nsub_mr = -1;            // analysis sub-tiles per axis (-1 = whole blocks, measured best)
   int tpb_mr = 256;            // analysis threads per workgroup for whole blocks (tuned)
-  int nsub_ref = 0;            // refinement sub-tiles per axis (0 = choose by work count)
   int order = 0;               // stage processing order: 0 forest (Morton), 1 level-sorted
   std::string tune_log;
   // captured step graphs (refine, four stages, first analysis), keyed by launch parameters
@@ -301,7 +300,7 @@ struct mrb_ctx {
   // paths until each has ten samples, then the faster median wall time wins)
   int graph_mode = 2;
   std::vector<double> probe_us[2];
-  struct GraphEntry { uint64_t key[7 + sizeof(TopoHeader) / 8]; hipGraphExec_t exec; };
+  struct GraphEntry { uint64_t key[6 + sizeof(TopoHeader) / 8]; hipGraphExec_t exec; };
   std::vector<GraphEntry> graphs;
   long n_graph_launches = 0;
   // host-side time (microseconds) by phase
@@ -905,22 +904,14 @@ Variant pick_stage(const mrb_ctx* c) {
 // threads per workgroup of the analysis kernel: the tuned choice for whole blocks
 int mr_tpb(const mrb_ctx* c, int nsub) { return nsub == 1 ? c->tpb_mr : 256; }
 
-// sub-tiles per axis for the analysis / refinement kernels: the smallest count whose
-// workgroups (n_items each) cover the chip twice
-int pick_aux(const mrb_ctx* c, long n_items, int forced = 0) {
+// sub-tiles per axis of the analysis: whole blocks (100 blocks of four fields: 10 us against
+// 32.5 us for quarters) unless tuning chose otherwise
+int pick_mr(const mrb_ctx* c) {
   int v[8];
-  const int nv = aux_variants(c->shape, 0, v, 8);
+  const int nv = aux_variants(c->shape, v, 8);
   for (int i = 0; i < nv; ++i)
-    if (forced && v[i] == forced) return forced;
-  if (forced < 0) return 1;  // whole blocks
-  if (c->shape.dim == 3) return 1;   // the column kernels, see pick_stage
-  std::sort(v, v + nv);
-  for (int i = 0; i < nv; ++i) {
-    long w = n_items;
-    for (int a = 0; a < c->cfg.dim; ++a) w *= v[i];
-    if (w >= 2L * c->ncu) return v[i];
-  }
-  return v[nv - 1];
+    if (v[i] == c->nsub_mr) return v[i];
+  return 1;
 }
 
 // launch one RK stage (fused) or ghost + RHS per level (plain)
@@ -1186,15 +1177,12 @@ bool refine_foldable(const mrb_ctx* c) {
   return !c->leaves.empty() && c->leaves[0].level < c->cfg.jmax && !c->dev.active;
 }
 
-// refinement kernel over the uploaded plan (nref parents); fixed_grid for graph capture
-mrb_status launch_refine_kernel(mrb_ctx* c, int nref, bool fixed_grid) {
+// refinement kernel over the uploaded plan (nref parents)
+mrb_status launch_refine_kernel(mrb_ctx* c, int nref) {
   const int nch = 1 << c->cfg.dim;
   RefineArgs a{topo(c), c->u};
-  const int ns = pick_aux(c, (long)nref * nch, c->nsub_ref);
-  long work = (long)nref * nch;
-  for (int q = 0; q < c->cfg.dim; ++q) work *= ns;
   TimeScope ts(c, T_REFINE, (double)nref * c->bsz * 8.0 * (1 + nch));
-  HIPCHK(c, launch_refine(c->shape, ns, fixed_grid ? c->grid : grid_for(c, work), a, c->stream));
+  HIPCHK(c, launch_refine(c->shape, a, c->stream));
   return MRB_OK;
 }
 
@@ -1230,7 +1218,7 @@ mrb_status do_refine(mrb_ctx* c, const std::vector<int>& par, bool launch, bool 
       c->have_flags = false;
       c->pending_ref = e->pending_ref;
       if (!launch) return MRB_OK;
-      return launch_refine_kernel(c, c->pending_ref, false);
+      return launch_refine_kernel(c, c->pending_ref);
     }
   }
   c->hcount_ref_zero = false;
@@ -1293,7 +1281,7 @@ mrb_status do_refine(mrb_ctx* c, const std::vector<int>& par, bool launch, bool 
       (s = memo_record(c, mask ? 2 : 0, material, taken.size(), freed, c->pending_ref, 0, (int)par.size())))
     return s;
   if (!launch) return MRB_OK;
-  return launch_refine_kernel(c, c->pending_ref, false);
+  return launch_refine_kernel(c, c->pending_ref);
 }
 
 MrArgs mr_args(mrb_ctx* c) {
@@ -1314,7 +1302,7 @@ mrb_status launch_mr_kernel(mrb_ctx* c, bool fixed_grid, const mrb_ctx::Memo* sp
   const int n = (int)nblk(c);
   MrArgs a = mr_args(c);
   if (spec) a.smap = spec->smap;
-  const int ns = pick_aux(c, n, c->nsub_mr);
+  const int ns = pick_mr(c);
   long work = n;
   for (int q = 0; q < c->cfg.dim; ++q) work *= ns;
   TimeScope ts(c, T_MR, (double)n * c->bsz * 8.0);
@@ -1827,7 +1815,7 @@ mrb_status issue_step(mrb_ctx* c, double t, double dt, Issued& is, int* state) {
   if (r) return r;
   if (!spec_all_merge(c)) {
     // the refinement is done but the step cannot be one launch: finish it the usual way
-    if ((r = launch_refine_kernel(c, c->pending_ref, false))) return r;
+    if ((r = launch_refine_kernel(c, c->pending_ref))) return r;
     bool tiled = false;
     if ((r = rk4_adapt_tiled(c, t, dt, &tiled, false))) return r;
     if (!tiled && (r = do_rk4(c, t, dt))) return r;
@@ -1961,23 +1949,22 @@ mrb_status step_graph(mrb_ctx* c, double t, double dt) {
   uint64_t dtb;
   std::memcpy(&dtb, &dt, sizeof dtb);
   const Variant vs = pick_stage(c);
-  const int nsm = pick_aux(c, (long)c->hblk.size(), c->nsub_mr);
-  const int nsr = pick_aux(c, (long)std::max(1, c->pending_ref) << c->cfg.dim, c->nsub_ref);
+  const int nsm = pick_mr(c);
   // the first analysis pass writes the speculated coarsening's mothers when there is one
   // (its map is read at replay time from the memo's device copy)
   mrb_ctx::Memo* se = spec_entry(c);
   const int* smap = se ? se->smap : nullptr;
   // the launches take the topology header by value: a replay needs the same header
-  uint64_t key[7 + sizeof(TopoHeader) / 8] = {
+  uint64_t key[6 + sizeof(TopoHeader) / 8] = {
       (uint64_t)(uintptr_t)c->u, (uint64_t)vs.nsub | ((uint64_t)c->order << 8) | ((uint64_t)vs.tpb << 16),
-      (uint64_t)nsm, (uint64_t)nsr, dtb, (uint64_t)(uintptr_t)c->arena, (uint64_t)(uintptr_t)smap};
-  std::memcpy(key + 7, &c->arena_hdr, sizeof(TopoHeader));
+      (uint64_t)nsm, dtb, (uint64_t)(uintptr_t)c->arena, (uint64_t)(uintptr_t)smap};
+  std::memcpy(key + 6, &c->arena_hdr, sizeof(TopoHeader));
   hipGraphExec_t exec = nullptr;
   for (auto& g : c->graphs)
     if (std::memcmp(g.key, key, sizeof key) == 0) exec = g.exec;
   if (!exec) {
     HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-    mrb_status e = launch_refine_kernel(c, std::max(1, c->pending_ref), true);
+    mrb_status e = launch_refine_kernel(c, std::max(1, c->pending_ref));
     if (!e) e = sweep(c, t, dt, true);
     double* u0 = c->u;
     if (!e) {
@@ -2324,7 +2311,7 @@ mrb_status dev_refine_all(mrb_ctx* c) {
   c->pending_ref = nref;
   c->n_refined += nref;
   c->have_flags = false;
-  return launch_refine_kernel(c, nref, false);
+  return launch_refine_kernel(c, nref);
 }
 
 // analysis and coarsening until nothing merges, planned on the device; one read-back
@@ -2339,7 +2326,7 @@ mrb_status dev_adapt(mrb_ctx* c, int* npass) {
       MrArgs m = mr_args(c);
       m.flags = D.flags;
       m.maxd = D.maxd;
-      const int ns = pick_aux(c, n, c->nsub_mr);
+      const int ns = pick_mr(c);
       long work = n;
       for (int q = 0; q < c->cfg.dim; ++q) work *= ns;
       TimeScope ts(c, T_MR, (double)n * c->bsz * 8.0);
@@ -2724,7 +2711,7 @@ mrb_status mrb_mr_pass_noalloc(mrb_ctx* c, int8_t* flags, double* maxd) {
                                        " fields exceed the " + std::to_string(kScratchBytes) + "-byte scratch");
   // sub-tiled workgroups: the tuned analysis tiling when it is sub-tiled, else 2 per axis
   int va[8];
-  const int na = aux_variants(c->shape, 0, va, 8);
+  const int na = aux_variants(c->shape, va, 8);
   int ns = c->nsub_mr > 1 ? c->nsub_mr : 2;
   bool compiled = false;
   for (int i = 0; i < na; ++i) compiled = compiled || va[i] == ns;
@@ -3206,7 +3193,7 @@ mrb_status mrb_tune(mrb_ctx* c, int nsub, int reps, double dt, int* chosen) {
                 if (m < ac.size()) {
                   r = launch_tiled(c, ac[m].nsub, ra, true, ac[m].tpb, true);
                 } else {
-                  r = launch_refine_kernel(c, c->pending_ref, false);
+                  r = launch_refine_kernel(c, c->pending_ref);
                   if (!r) r = launch_tiled(c, c->ana_nsub, ra, true, c->ana_tpb);
                 }
               }
@@ -3281,12 +3268,12 @@ mrb_status mrb_tune(mrb_ctx* c, int nsub, int reps, double dt, int* chosen) {
         }
       }
     }
-    // analysis and refinement tilings: several rounds over the candidates, the fastest
+    // analysis tilings: several rounds over the candidates, the fastest
     // round of each counts (single launches of these kernels are a few microseconds on
     // small grids, where one round is at the mercy of noise)
     int va[8];
-    const int na = aux_variants(c->shape, 0, va, 8);
-    auto time_variants = [&](const char* name, int* choice, auto&& run) -> mrb_status {
+    const int na = aux_variants(c->shape, va, 8);
+    auto time_variants = [&](const char* name, int* choice, int na, auto&& run) -> mrb_status {
       float best_v[8];
       for (int i = 0; i < na; ++i) best_v[i] = 1e30f;
       for (int round = 0; round < kRounds; ++round)
@@ -3320,7 +3307,7 @@ mrb_status mrb_tune(mrb_ctx* c, int nsub, int reps, double dt, int* chosen) {
       mrb_status r = do_mr_pass(c);
       if (r && r != MRB_E_NONFINITE) return done(r);
     }
-    mrb_status tr = time_variants("mr", &c->nsub_mr, [&](int v, int k) -> mrb_status {
+    mrb_status tr = time_variants("mr", &c->nsub_mr, na, [&](int v, int k) -> mrb_status {
       MrArgs a = mr_args(c);
       const int n = (int)c->hblk.size();
       long work = n;
@@ -3364,9 +3351,10 @@ mrb_status mrb_tune(mrb_ctx* c, int nsub, int reps, double dt, int* chosen) {
     // refinement, while the last refinement plan is still the uploaded one: re-running
     // it rewrites the same children from the untouched parents
     if (c->pending_ref > 0) {
-      tr = time_variants("refine", &c->nsub_ref, [&](int, int k) -> mrb_status {
+      int whole = 1;   // (timed for the log: whole children are the only form)
+      tr = time_variants("refine", &whole, 1, [&](int, int k) -> mrb_status {
         for (int j = 0; j < k; ++j) {
-          mrb_status r = launch_refine_kernel(c, c->pending_ref, false);
+          mrb_status r = launch_refine_kernel(c, c->pending_ref);
           if (r) return r;
         }
         return MRB_OK;
@@ -3379,7 +3367,6 @@ mrb_status mrb_tune(mrb_ctx* c, int nsub, int reps, double dt, int* chosen) {
     c->tpb = 256;
     c->nsub_mr = -1;
     c->tpb_mr = 256;
-    c->nsub_ref = 0;
     c->order = 0;
     c->rk4t_nsub = 0;
     c->rk4t_tuned = false;

@@ -537,6 +537,267 @@ __global__ void __launch_bounds__(NST) k_filter2(FilterArgs A) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// Prediction over a block's 33^2 (17^2) points from an EW^2 array of every second one and one
+// more around them (the even points of the block, or the parent's points under a child): the
+// points between two along x are formed once (od), a point off the rows combines four of them.
+// ---------------------------------------------------------------------------
+template <int BS>
+struct Half2 {
+  static constexpr int M = (BS - 1) / 2, EW = M + 3, NE = EW * EW, NOUT = 4 * EW - 4;
+};
+
+template <int BS, int NF, int TPB>
+__device__ __forceinline__ void fill_odd2(double* od, const double* ev) {
+  constexpr int EW = Half2<BS>::EW, M = Half2<BS>::M;
+  for (int p = threadIdx.x; p < NF * EW * M; p += TPB) {
+    const double* e = ev + p % M + EW * (p / M);
+    od[p % M + EW * (p / M)] = P4(e[0], e[1], e[2], e[3]);
+  }
+}
+
+template <int BS>
+__device__ __forceinline__ double half_value(const double* ev, const double* od, int x, int y) {
+  constexpr int EW = Half2<BS>::EW;
+  const double* c = ((x & 1) ? od + x / 2 : ev + x / 2 + 1) + EW * (y / 2);
+  return (y & 1) ? P4(c[0], c[EW], c[2 * EW], c[3 * EW]) : c[EW];
+}
+
+// ---------------------------------------------------------------------------
+// Analysis of a whole block per workgroup (operations and stores as k_mr in kernels.hip):
+// a thread owns a few of the block's points, LDS holds only the even points and their odd
+// neighbours along x (6 KB a field, so that eight blocks of one field share a compute unit).
+// Bound by memory on large grids (4,096 blocks, 36 MB: 15.6 us against 39.7 for a tile in
+// LDS) and by its chain of loads on small ones (740 to 2,900 blocks: 7.4 against 12.9 us; four
+// fields, 740 to 2,900 blocks on five levels: 21.6 against 40.4 us).
+// ---------------------------------------------------------------------------
+template <int BS, int NF, int TPB>
+__global__ void __launch_bounds__(TPB) k_mr2(MrArgs A) {
+  using HB = Half2<BS>;
+  constexpr int NP = BS * BS, EW = HB::EW, NE = HB::NE, RG = TPB / BS, NR = (BS + RG - 1) / RG, ROWS = BS + 4;
+  static_assert(TPB >= HB::NOUT, "one even point outside the block per thread");
+  __shared__ Rows2<ROWS> zn;
+  __shared__ double ev[NF * NE], od[NF * NE];
+  __shared__ double red[TPB / 64][NF];
+  const XcdWork it(A.topo.h.n_blocks);   // one work item per workgroup
+  if (!it.ok()) return;
+  const int tid = threadIdx.x, b = it.w;
+  const BlockDesc d = A.topo.blk()[b];
+  const int sm = A.smap ? A.smap[b] : -1;
+  row_table<BS, NF, TPB>(zn, d, A.topo.nb(b), A.topo.h.nb_stride, -2);
+  const int base = d.slot * NF * NP;
+  const int x = tid % BS, rg = tid / BS, zx = zone_of<BS>(x);
+  double v[NR][NF];
+  unsigned in = 0, fine = 0;   // rows of the block; those a finer neighbour owns
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    const int y = rg + RG * i;
+    const bool ok = rg < RG && y < BS;
+    const SEnt E = zn.tab[zx + NZ * (min(y, BS - 1) + 2)];
+    if (ok) in |= 1u << i;
+    if (ok && E.sh == 0) fine |= 1u << i;
+    const int ad = ok ? E.base + ((2 * x) >> E.sh) : base;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) v[i][f] = (A.u + f * NP)[(unsigned)ad];
+  }
+  double ov[NF];
+  int oi = 0;
+  if (tid < HB::NOUT) {
+    // even points outside the block: the first and last rows, then the first and last columns
+    const int r = tid - 2 * EW;
+    const int cx = tid < 2 * EW ? tid % EW : (r & 1) * (EW - 1), cy = tid < 2 * EW ? (tid / EW) * (EW - 1) : 1 + r / 2;
+    const int sx = 2 * cx - 2, sy = 2 * cy - 2;
+    const SEnt E = zn.tab[zone_of<BS>(sx) + NZ * (sy + 2)];
+    const int ad = E.base + ((2 * sx) >> E.sh);
+    oi = cx + EW * cy;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) ov[f] = (A.u + f * NP)[(unsigned)ad];
+  }
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    const int y = rg + RG * i;
+    if (((in >> i) & 1u) && ((x | y) & 1) == 0) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f) ev[f * NE + x / 2 + 1 + EW * (y / 2 + 1)] = v[i][f];
+    }
+    // redundant nodes owned by a finer neighbour: store the synchronised value
+    if ((fine >> i) & 1u) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f) (A.u + f * NP)[(unsigned)(base + x + BS * y)] = v[i][f];
+    }
+  }
+  if (tid < HB::NOUT) {
+#pragma unroll
+    for (int f = 0; f < NF; ++f) ev[f * NE + oi] = ov[f];
+  }
+  __syncthreads();
+  fill_odd2<BS, NF, TPB>(od, ev);
+  __syncthreads();
+  // |details| as unsigned bits, whose maximum NaN propagates through (zero at even points)
+  unsigned long long m[NF] = {};
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    const int y = rg + RG * i;
+    if (!((in >> i) & 1u) || ((x | y) & 1) == 0) continue;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      const double dv = fabs(v[i][f] - half_value<BS>(ev + f * NE, od + f * NE, x, y));
+      m[f] = umax64(m[f], (unsigned long long)__double_as_longlong(dv));
+    }
+  }
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    const double w = wave_nanmax(__longlong_as_double((long long)m[f]));
+    if ((tid & 63) == 0) red[tid >> 6][f] = w;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    bool coarse = d.level > 1;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      double w = red[0][f];
+#pragma unroll
+      for (int q = 1; q < TPB / 64; ++q) w = nanmax(w, red[q][f]);
+      A.maxd[(size_t)b * NF + f] = w;
+      if (!(w < A.thr[f])) coarse = false;
+    }
+    A.flags[b] = coarse ? (int8_t)-1 : (int8_t)0;
+  }
+  if (sm >= 0) {
+    // the block is child `ch` of a speculated family: the mother's nodes it supplies (see
+    // k_mr3 in column3.hip)
+    const int ch = sm & 7, mbase = (sm >> 3) * NF * NP;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const int y = rg + RG * i;
+      if (!((in >> i) & 1u) || ((x | y) & 1) || ((ch & 1) && x == 0) || ((ch & 2) && y == 0)) continue;
+      const int mn = x / 2 + (ch & 1) * HB::M + BS * (y / 2 + ((ch >> 1) & 1) * HB::M);
+      const bool from_tile = !(x == 0 || y == 0 || x == BS - 1 || y == BS - 1) || ((fine >> i) & 1u);
+#pragma unroll
+      for (int f = 0; f < NF; ++f) {
+        double* u = A.u + f * NP;
+        u[(unsigned)(mbase + mn)] = from_tile ? v[i][f] : u[(unsigned)(base + x + BS * y)];
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Refinement, one workgroup per child of a parent (the child's nodes take the
+// synchronised value at level l+1: a finer neighbour's stored value where one holds the node,
+// else the parent's value at even nodes or its prediction at odd ones):
+// LDS holds the synchronised parent points the child needs, its half of the parent and one
+// point around.  Bound by its stores.  740 to 2,900 blocks of one field: 11.6 us against 15.1
+// for a tile; of four fields: 27.0 against 43.6 us.
+// ---------------------------------------------------------------------------
+template <int BS, int NF, int TPB>
+__global__ void __launch_bounds__(TPB) k_refine2(RefineArgs A) {
+  using HB = Half2<BS>;
+  constexpr int NP = BS * BS, M = HB::M, EW = HB::EW, NE = HB::NE, RG = TPB / BS, NR = (BS + RG - 1) / RG;
+  constexpr int LW = M / 2 + 5, NL = LW * LW, ROWS = 2 * LW - 1;   // the parent's coarse lattice
+  constexpr int RE = (NE + TPB - 1) / TPB;
+  static_assert(TPB >= NL && TPB >= 2 * EW, "one lattice point per thread");
+  __shared__ Rows2<ROWS> zn;
+  __shared__ double ev[NF * NE], od[NF * NE];   // od first holds the lattice
+  static_assert(NL <= NE, "the lattice fits od");
+  const XcdWork it(A.topo.h.n_ref * 4);   // one work item per workgroup
+  if (!it.ok()) return;
+  const int tid = threadIdx.x, ri = it.w >> 2, ch = it.w & 3, bx = ch & 1, by = ch >> 1;
+  const BlockDesc d = A.topo.pblk()[ri];
+  const int obase = A.topo.ref()[ri].child[ch] * NF * NP;
+  const int l0 = M * bx - 4, l1 = M * by - 4;   // first lattice point
+  row_table<BS, NF, TPB>(zn, d, A.topo.pnb(ri), A.topo.h.pnb_stride, l1);
+  // finer entries come last in the list
+  const bool hasc = d.n_coarse > 0, hasf = d.n_ent > 0 && zn.se[d.n_ent - 1].sh == 0;
+  const int base = d.slot * NF * NP;
+  auto owner = [&](int sx, int sy) { return zn.tab[zone_of<BS>(sx) + NZ * (sy - l1)]; };
+  double pv[RE][NF];
+#pragma unroll
+  for (int q = 0; q < RE; ++q) {
+    const int p = min(tid + q * TPB, NE - 1);
+    const int sx = l0 + 3 + p % EW, sy = l1 + 3 + p / EW;
+    const SEnt E = owner(sx, sy);
+    const int ad = E.sh < 2 || ((sx | sy) & 1) == 0 ? E.base + ((2 * sx) >> E.sh) : base;   // (unheld: predicted below)
+#pragma unroll
+    for (int f = 0; f < NF; ++f) pv[q][f] = (A.u + f * NP)[(unsigned)ad];
+  }
+  double lv[NF];
+  if (hasc) {
+    const int p = min(tid, NL - 1), sx = l0 + 2 * (p % LW), sy = l1 + 2 * (p / LW);
+    const SEnt E = owner(sx, sy);
+    const int ad = E.base + ((2 * sx) >> E.sh);
+#pragma unroll
+    for (int f = 0; f < NF; ++f) lv[f] = (A.u + f * NP)[(unsigned)ad];
+  }
+  const int x = tid % BS, rg = tid / BS;
+  // odd nodes of the parent's boundary that a finer leaf holds take its value: their address
+  int fa[NR];
+#pragma unroll
+  for (int i = 0; i < NR; ++i) fa[i] = -1;
+  if (hasf) {
+    // zone of a fine coordinate Q (parent coordinate Q / 2)
+    auto fz = [](int Q) { return Q == 0 ? 1 : (Q < BS - 1 ? 2 : (Q == BS - 1 ? 3 : (Q < 2 * (BS - 1) ? 4 : 5))); };
+    const int lane = tid & 63;
+    const unsigned long long fmask = __ballot(lane < d.n_ent && zn.se[lane].sh == 0);
+    const int Qx = x + (BS - 1) * bx;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const int y = min(rg + RG * i, BS - 1), Qy = y + (BS - 1) * by;
+      const unsigned long long c = zn.m[0][fz(Qx)] & zn.m[1][fz(Qy)] & fmask;
+      const bool rim = Qx == 0 || Qx == 2 * (BS - 1) || Qy == 0 || Qy == 2 * (BS - 1);
+      if (rim && ((x | y) & 1) && c) fa[i] = zn.se[__ffsll((long long)c) - 1].base + Qx + BS * Qy;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < RE; ++q) {
+    const int p = tid + q * TPB;
+    if (p < NE) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f) ev[f * NE + p] = pv[q][f];
+    }
+  }
+  if (hasc) {
+    if (tid < NL) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f) od[f * NE + tid] = lv[f];
+    }
+    __syncthreads();
+    // parent points inside a coarser neighbour, off its lattice: only the row and the column
+    // one point outside the parent can hold any
+    if (tid < 2 * EW) {
+      const bool col = tid >= EW;
+      const int k = tid % EW, e0 = bx ? EW - 1 : 0, e1 = by ? EW - 1 : 0;
+      const int c0 = col ? e0 : k, c1 = col ? k : e1;
+      const int sx = l0 + 3 + c0, sy = l1 + 3 + c1;
+      if (owner(sx, sy).sh == 2 && ((sx | sy) & 1)) {
+        const int t0 = c0 + 3, t1 = c1 + 3;   // from the lattice's first point
+        const int px = t0 & 1, py = t1 & 1;
+        const double* c = od + (px ? (t0 - 3) / 2 : t0 / 2) + LW * (py ? (t1 - 3) / 2 : t1 / 2);
+#pragma unroll
+        for (int f = 0; f < NF; ++f, c += NE) {
+          auto row = [&](const double* q) { return px ? P4(q[0], q[1], q[2], q[3]) : q[0]; };
+          ev[f * NE + c0 + EW * c1] = py ? P4(row(c), row(c + LW), row(c + 2 * LW), row(c + 3 * LW)) : row(c);
+        }
+      }
+    }
+  }
+  __syncthreads();
+  fill_odd2<BS, NF, TPB>(od, ev);
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    const int y = rg + RG * i;
+    if (rg >= RG || y >= BS) continue;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      double* u = A.u + f * NP;
+      double w = half_value<BS>(ev + f * NE, od + f * NE, x, y);
+      if (fa[i] >= 0) w = u[(unsigned)fa[i]];
+      u[(unsigned)(obase + x + BS * y)] = w;
+    }
+  }
+}
+
 // one workgroup per work item (XcdWork deals them out from a multiple of 8)
 template <typename K, typename Arg>
 hipError_t go2(K kern, int items, size_t lds, int threads, hipStream_t st, const Arg& a) {
@@ -562,6 +823,28 @@ hipError_t launch_stage2(const Shape& s, int precision, const StageArgs& a, hipS
   }
   if (precision == 0) return go2(k_stage2<17, 448, double, double>, n, 0, 448, st, a);
   return go2(k_stage2<17, 448, float, float>, n, 0, 448, st, a);
+}
+
+// The analysis takes 256 threads a block unless tuning asks for more (4,096 blocks of 33^2:
+// 15.6 us with 256, 20.3 with 512, 33.6 with 576; 100 blocks of four fields: 10.9, 10.1 with
+// 512, 12.8 with 1,024), the one round of 17^2 points a multiple of 64 that holds them; the
+// refinement 256 (one field: 11.6 us against 12.2 with 512) or 512 (four: 27.0 against 27.6
+// with 256 and 36.9 with 576).
+hipError_t launch_mr2(const Shape& s, int tpb, const MrArgs& a, hipStream_t st) {
+  const int n = a.topo.h.n_blocks;
+  if (s.bs == 17) return tpb == 256 ? go2(k_mr2<17, 1, 320>, n, 0, 320, st, a) : hipErrorInvalidValue;
+  if (tpb == 256) return s.nf == 4 ? go2(k_mr2<33, 4, 256>, n, 0, 256, st, a) : go2(k_mr2<33, 1, 256>, n, 0, 256, st, a);
+  if (tpb == 512) return s.nf == 4 ? go2(k_mr2<33, 4, 512>, n, 0, 512, st, a) : go2(k_mr2<33, 1, 512>, n, 0, 512, st, a);
+  if (tpb == 1024)
+    return s.nf == 4 ? go2(k_mr2<33, 4, 1024>, n, 0, 1024, st, a) : go2(k_mr2<33, 1, 1024>, n, 0, 1024, st, a);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_refine2(const Shape& s, const RefineArgs& a, hipStream_t st) {
+  const int n = 4 * a.topo.h.n_ref;
+  if (s.nf == 4) return go2(k_refine2<33, 4, 512>, n, 0, 512, st, a);
+  if (s.bs == 33) return go2(k_refine2<33, 1, 256>, n, 0, 256, st, a);
+  return go2(k_refine2<17, 1, 320>, n, 0, 320, st, a);
 }
 
 hipError_t launch_filter(const FilterArgs& a, hipStream_t st) {

@@ -1212,3 +1212,37 @@ def test_device_topology_on_ragged_and_wide_grids(case):
     assert 4 < len(out[0][0]) < 40000 and len(set(out[0][0].tolist())) > 1
     for a, b in zip(*out):
         assert np.array_equal(_bits(a) if a.dtype == np.float64 else a, _bits(b) if b.dtype == np.float64 else b)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("which", ["C1", "C2", "C3"])
+@pytest.mark.parametrize("seed,p_refine", [(0, 0.45), (3, 0.3), (5, 0.7)])
+def test_2d_analysis_and_refinement_on_ragged_forests(which, seed, p_refine):
+    """The analysis of whole 2D blocks (flags, maxima, written-back nodes, each workgroup size),
+    the refinement and an adaptation on random graded forests of rough data: bitwise against
+    the oracle."""
+    make = {"C1": W.C1, "C2": W.C2, "C3": W.C3}[which]
+    cfg = make(jmax=5, form=W.FORM_FUSED, max_blocks=3000)
+    lv, co = W.random_graded_forest(2, 4, seed, p_refine)
+    for tpb in (256,) if which == "C1" else (256, 512, 1024):
+        s, o = M.Solver(cfg), oracle.Oracle(cfg)
+        o.init_forest(lv, co)
+        lv, co = o.read_forest()
+        data = W.sample(cfg, lv, co)
+        data = data + 1e-3 * np.cos(37.0 * data)          # details of every size
+        s.init_forest(lv, co)
+        s.load_blocks(data)
+        o.load_blocks(data)
+        if tpb > 256:
+            s.tune(nsub=2 if which == "C3" else 1, reps=-tpb)
+        assert s.stats()["analysis_threads"] == tpb
+        f1, m1 = s.mr_pass()
+        f2, m2 = o.mr_pass()
+        assert np.array_equal(f1, f2) and np.array_equal(m1, m2)
+        assert np.array_equal(s.read_blocks(), o.read_blocks())
+        s.refine_all()
+        o.refine_all()
+        assert np.array_equal(s.read_blocks(), o.read_blocks())
+        assert s.adapt() == o.adapt()
+        assert np.array_equal(s.read_blocks(), o.read_blocks())
+        s.close()
