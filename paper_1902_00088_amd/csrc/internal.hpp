@@ -230,7 +230,7 @@ hipError_t launch_stage2(const Shape& s, int precision, const StageArgs& a, hipS
 hipError_t launch_filter(const FilterArgs& a, hipStream_t st);   // NS shape only
 // threads of the zone-owner stage kernel of a shape (column3.hip, plane2.hip)
 inline int zone_threads(const Shape& s) {
-  return s.dim == 3 ? kColumnThreads : (s.nf == 4 ? kNsThreads : (s.bs == 33 ? 576 : 448));
+  return s.dim == 3 ? kColumnThreads : (s.nf == 4 ? kNsThreads : (s.bs == 33 ? 384 : 448));
 }
 hipError_t launch_plain(const Shape& s, int grid, const StageArgs& a, hipStream_t st);  // ghost + RHS kernels
 // overlapped-tile RK4 step; hipErrorInvalidValue if the shape has no such kernel

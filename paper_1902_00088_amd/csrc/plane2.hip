@@ -205,9 +205,11 @@ __device__ __forceinline__ void with_source(const StageArgs& A, const F& f) {
 
 // ---------------------------------------------------------------------------
 // Advection stage (constant velocity or swirl) of a whole block per workgroup, one (17^2) or
-// two to three (33^2) tile points per thread.  Latency bound: the descriptor and entry row,
-// the owner table, one round of loads, LDS, the update.  1,400 blocks of 33^2 FP64: 15.8 us a
-// stage against 22.3 us; 40 blocks of 17^2: 5.3 against 6.5 us.
+// four (33^2) tile points per thread.  Latency bound: the descriptor and entry row, the owner
+// table, one round of loads, LDS, the update; so the workgroup size trades rounds against
+// blocks in flight.  740 to 2,900 blocks of 33^2 FP64: 12.9 us a stage with 384 threads (13.7
+// with 256, 15.8 with 576) against 22.3 us for a tile gathered point by point; 40 blocks of
+// 17^2: 5.3 us with 448 (5.8 with 256) against 6.5 us.
 // ---------------------------------------------------------------------------
 template <int BS, int TPB, typename TT, typename KT>
 __global__ void __launch_bounds__(TPB) k_stage2(StageArgs A) {
@@ -818,8 +820,8 @@ hipError_t launch_stage2(const Shape& s, int precision, const StageArgs& a, hipS
     return go2(k_stage_ns<float, float>, NPART * n, NsLds<float, float>::bytes, NST, st, a);
   }
   if (s.bs == 33) {
-    if (precision == 0) return go2(k_stage2<33, 576, double, double>, n, 0, 576, st, a);
-    return go2(k_stage2<33, 576, float, float>, n, 0, 576, st, a);
+    if (precision == 0) return go2(k_stage2<33, 384, double, double>, n, 0, 384, st, a);
+    return go2(k_stage2<33, 384, float, float>, n, 0, 384, st, a);
   }
   if (precision == 0) return go2(k_stage2<17, 448, double, double>, n, 0, 448, st, a);
   return go2(k_stage2<17, 448, float, float>, n, 0, 448, st, a);

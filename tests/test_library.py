@@ -1151,7 +1151,7 @@ def test_2d_zone_kernels_on_ragged_forests(which, seed, p_refine):
     s.init_forest(lv, co)
     s.load_blocks(data)
     o.load_blocks(data)
-    zoned = {"C1": 448}.get(which, 576)
+    zoned = {"C1": 448, "C2": 384, "C2t": 384}.get(which, 576)
     assert s.stats()["stage_threads"] == (zoned if which == "C1" or len(lv) > 16 else 256)
     for k in range(2):
         s.rk4(k * cfg.dt, cfg.dt)
