@@ -1246,3 +1246,48 @@ def test_2d_analysis_and_refinement_on_ragged_forests(which, seed, p_refine):
         assert s.adapt() == o.adapt()
         assert np.array_equal(s.read_blocks(), o.read_blocks())
         s.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dim", [2, 3])
+def test_init_forest_refusals_leave_the_forest(dim):
+    """Overlaps (a leaf's child, its last descendant, its parent), duplicates, holes and level
+    jumps are refused in any order of the blocks, and the forest before stays usable; blocks in
+    any order give the same forest and entries (values read back after a stage)."""
+    cfg = W.C1(jmax=5) if dim == 2 else W.C4(jmax=4, max_blocks=3000)
+    lv, co = W.random_graded_forest(dim, 4 if dim == 2 else 3, 3, 0.4)
+    lv, co = np.asarray(lv, np.int8), np.asarray(co, np.int32)
+    s, o = M.Solver(cfg), oracle.Oracle(cfg)
+    o.init_forest(lv, co)
+    lv0, co0 = o.read_forest()
+    data = W.sample(cfg, lv0, co0)
+    o.load_blocks(data)
+    o.rk4(0.0, cfg.dt)
+    rng = np.random.default_rng(5)
+    p = rng.permutation(len(lv))
+    s.init_forest(lv[p], co[p])
+    small = int(np.argmin(lv))
+    fine = int(np.argmax(lv))
+    bad = [("overlap", np.r_[lv, lv[small] + 1], np.r_[co, 2 * co[small:small + 1]]),
+           ("overlap", np.r_[lv, lv[small] + 1], np.r_[co, 2 * co[small:small + 1] + 1]),
+           ("overlap", np.r_[lv, lv[fine] - 1], np.r_[co, co[fine:fine + 1] // 2]),
+           ("duplicate", np.r_[lv, lv[small]], np.r_[co, co[small:small + 1]]),
+           ("tile", np.delete(lv, small), np.delete(co, small, 0))]
+    jump = W.random_graded_forest(dim, 2, 0, 0.0)      # uniform level 1, one block to level 3
+    kids = np.indices((4,) * dim).reshape(dim, -1).T
+    bad.append(("graded", np.r_[jump[0][1:], np.full(len(kids), 3)],
+                np.r_[jump[1][1:], 4 * np.asarray(jump[1][:1]) + kids]))
+    for what, l2, c2 in bad:
+        q = rng.permutation(len(l2))
+        with pytest.raises(M.MrbError, match=what) as e:
+            s.init_forest(np.asarray(l2, np.int8)[q], np.asarray(c2, np.int32)[q])
+        assert e.value.code == -3
+    a, b = s.read_forest(), (lv0, co0)
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+    s.load_blocks(data)
+    s.rk4(0.0, cfg.dt)
+    assert np.array_equal(_bits(s.read_blocks()), _bits(o.read_blocks()))
+    s.refine_all()
+    o.refine_all()
+    assert_same(s, o, "refinement after refusals")
+    s.close()
