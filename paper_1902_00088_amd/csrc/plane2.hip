@@ -293,10 +293,10 @@ __global__ void __launch_bounds__(TPB) k_stage2(StageArgs A) {
 // formed once per tile point (it had cost eight FP64 divisions per flux point), and a
 // node's gradients, stresses and momentum factors pass from its fluxes to its right-hand
 // side in registers.  Bound by vector instructions (4,800 a half block, half of their
-// issue slots), LDS reads (40 of 100 us) and memory (260 MB, 50 us) together, overlapped by
-// the two workgroups that fit a compute unit's LDS; thirds of blocks (three workgroups) are
-// no faster, quarters slower.  2,944 blocks on five levels: 100 us a stage mixed against
-// 244 us for whole blocks of 256 threads; 1,024 blocks FP64: 43 against 76 us.
+// issue slots), LDS reads (40 us) and memory (260 MB, 50 us) together, overlapped by the two
+// or three workgroups that fit a compute unit's LDS; thirds of blocks are no faster, quarters
+// slower.  2,944 blocks on five levels: 94.5 us a stage mixed (100 with two workgroups a
+// compute unit) against 244 us for whole blocks of 256 threads; 1,024 blocks FP64: 43 against 76 us.
 // ---------------------------------------------------------------------------
 constexpr int NB = 33, NSY = 17, NST = kNsThreads, NPART = (NB + NSY - 1) / NSY;
 
@@ -306,19 +306,23 @@ __device__ __forceinline__ CT D4d(double um2, double um1, double up1, double up2
   else return (8.0f * (CT)(up1 - um1) - (CT)(up2 - um2)) * r;
 }
 
-template <typename KT, typename CT>
+// SHARE: the coarse lattice lies where the tile comes to lie and the heat fluxes take the place
+// of the normal stresses once these are read, three barriers more; in FP32 a third workgroup
+// fits the compute unit's LDS then
+template <typename KT, typename CT, bool SHARE>
 struct NsLds {
   using T2 = Tile2<NB, 4, 4, NSY, NST>;
   static constexpr int FX = NB + 4, FY = NSY + 4;            // flux points -2 .. 34, -2 .. cnt + 1
   static constexpr int NXX = FX * NSY, NYY = NB * FY, NXY = FX * FY;
   static constexpr size_t tile = sizeof(double) * T2::TSZ * 5;   // four fields and p / rho
-  static constexpr size_t flux = sizeof(CT) * (2 * NXX + 2 * NYY + NXY), lat = sizeof(double) * 2 * 4 * T2::CSZ;
-  static constexpr size_t bytes = tile + (flux > lat ? flux : lat);   // (the lattice is dead before the fluxes)
+  static constexpr size_t flux = sizeof(CT) * ((SHARE ? 1 : 2) * (NXX + NYY) + NXY), lat = sizeof(double) * 2 * 4 * T2::CSZ;
+  static constexpr size_t bytes = tile + (SHARE || flux > lat ? flux : lat);
+  static_assert(lat <= tile, "the lattice is dead before the tile (SHARE) or the fluxes are written");
 };
 
-template <typename KT, typename CT>
+template <typename KT, typename CT, bool SHARE>
 __global__ void __launch_bounds__(NST) k_stage_ns(StageArgs A) {
-  using L = NsLds<KT, CT>;
+  using L = NsLds<KT, CT, SHARE>;
   using G = Gather2<NB, 4, 4, NSY, NST, double>;
   using T2 = typename G::T2;
   constexpr int TW = T2::TW, TSZ = T2::TSZ, NP = T2::NP, HW = 4, FX = L::FX;
@@ -326,12 +330,12 @@ __global__ void __launch_bounds__(NST) k_stage_ns(StageArgs A) {
   extern __shared__ __align__(16) char smem[];
   double* tile = reinterpret_cast<double*>(smem);
   double* Tt = tile + 4 * TSZ;                       // p / rho
-  double* carr = Tt + TSZ;
-  CT* txx = reinterpret_cast<CT*>(carr);             // x -2..34, y 0..16
-  CT* qx = txx + L::NXX;
-  CT* tyy = qx + L::NXX;                             // x 0..32, y -2..18
-  CT* qy = tyy + L::NYY;
-  CT* txy = qy + L::NYY;                             // x -2..34, y -2..18
+  double* carr = SHARE ? tile : Tt + TSZ;
+  CT* txy = reinterpret_cast<CT*>(Tt + TSZ);         // x -2..34, y -2..18
+  CT* txx = txy + L::NXY;                            // x -2..34, y 0..16
+  CT* tyy = txx + L::NXX;                            // x 0..32, y -2..18
+  CT* qx = SHARE ? txx : tyy + L::NYY;
+  CT* qy = SHARE ? tyy : qx + L::NXX;
   const XcdWork it(NPART * A.topo.h.n_blocks);       // one work item per workgroup
   if (!it.ok()) return;
   const int tid = threadIdx.x, part = it.w % NPART;
@@ -344,6 +348,7 @@ __global__ void __launch_bounds__(NST) k_stage_ns(StageArgs A) {
     G g;
     const StageValue<double> val{A.alpha, A.off};
     with_source<KT>(A, [&](const auto& src) { g.run(carr, zn, base, d.n_coarse > 0, y0, cnty, src, val); });
+    if (SHARE && d.n_coarse > 0) __syncthreads();
 #pragma unroll
     for (int i = 0; i < T2::NR; ++i) {
       if (!((g.in >> i) & 1u)) continue;
@@ -389,40 +394,53 @@ __global__ void __launch_bounds__(NST) k_stage_ns(StageArgs A) {
     txx[wx] = sxx;
     tyy[wy] = syy;
     txy[wc] = sxy;
-    qx[wx] = -(kap * Dx(Tt, q));
-    qy[wy] = -(kap * Dy(Tt, q));
   }
-  {
-    const int p = NST - 1 - tid;                     // the last waves have fewer own nodes
-    const int nside = 4 * cnty;
-    if (p < nside + 4 * NB) {
-      const bool xs = p < nside;                     // beside the region along x
-      const int k = xs ? p % 4 : (p - nside) / NB;
-      const int fx = xs ? (k < 2 ? k - 2 : NB - 2 + k) : (p - nside) % NB;
-      const int fy = xs ? p / 4 : (k < 2 ? k - 2 : cnty - 2 + k);
-      const int s = fx + HW + TW * (fy + HW);
-      const CT ax = Dx(fu, s), ay = Dy(fu, s), bx = Dx(fv, s), by = Dy(fv, s);
-      const CT div = ax + by;
-      txy[fx + 2 + FX * (fy + 2)] = mu * (ay + bx);
-      if (xs) {
-        txx[fx + 2 + FX * fy] = mu * (CT(2) * ax - c23 * div);
-        qx[fx + 2 + FX * fy] = -(kap * Dx(Tt, s));
-      } else {
-        tyy[fx + NB * (fy + 2)] = mu * (CT(2) * by - c23 * div);
-        qy[fx + NB * (fy + 2)] = -(kap * Dy(Tt, s));
-      }
+  // beside the region along x (xs) or y
+  const int sp = NST - 1 - tid, nside = 4 * cnty;    // the last waves have fewer own nodes
+  const bool side = sp < nside + 4 * NB, xs = sp < nside;
+  const int sk = xs ? sp % 4 : (sp - nside) / NB;
+  const int fx = xs ? (sk < 2 ? sk - 2 : NB - 2 + sk) : (sp - nside) % NB;
+  const int fy = xs ? sp / 4 : (sk < 2 ? sk - 2 : cnty - 2 + sk);
+  const int s = fx + HW + TW * (fy + HW), ws = xs ? fx + 2 + FX * fy : fx + NB * (fy + 2);
+  if (side) {
+    const CT ax = Dx(fu, s), ay = Dy(fu, s), bx = Dx(fv, s), by = Dy(fv, s);
+    const CT div = ax + by;
+    txy[fx + 2 + FX * (fy + 2)] = mu * (ay + bx);
+    if (xs) txx[ws] = mu * (CT(2) * ax - c23 * div);
+    else tyy[ws] = mu * (CT(2) * by - c23 * div);
+  }
+  auto heat = [&]() {
+    if (mine) {
+      qx[wx] = -(kap * Dx(Tt, q));
+      qy[wy] = -(kap * Dy(Tt, q));
     }
-  }
+    if (side) {
+      if (xs) qx[ws] = -(kap * Dx(Tt, s));
+      else qy[ws] = -(kap * Dy(Tt, s));
+    }
+  };
+  auto dxw = [&](const CT* w, int i) { return D4(w[i - 2], w[i - 1], w[i + 1], w[i + 2], r); };
+  auto dyw = [&](const CT* w, int i, int t) { return D4(w[i - 2 * t], w[i - t], w[i + t], w[i + 2 * t], r); };
+  if constexpr (!SHARE) heat();
   __syncthreads();
+  CT dtxx, dtxy_y, dtxy_x, dtyy;
+  if (mine) {
+    dtxx = dxw(txx, wx);
+    dtyy = dyw(tyy, wy, NB);
+    dtxy_y = dyw(txy, wc, FX);
+    dtxy_x = dxw(txy, wc);
+  }
+  if constexpr (SHARE) {
+    __syncthreads();
+    heat();
+    __syncthreads();
+  }
   if (mine) {
     const size_t node = (size_t)base + lx + NB * (y0 + ly);
     const CT rho = (CT)fr[q], uu = (CT)fu[q], vv = (CT)fv[q], pp = (CT)fp[q];
     const CT px = Dx(fp, q), py = Dy(fp, q);
     const CT dmx = D4d<CT>(fr[q - 2] * um[0], fr[q - 1] * um[1], fr[q + 1] * um[2], fr[q + 2] * um[3], r);
     const CT dmy = D4d<CT>(fr[q - 2 * TW] * vm[0], fr[q - TW] * vm[1], fr[q + TW] * vm[2], fr[q + 2 * TW] * vm[3], r);
-    auto dxw = [&](const CT* w, int i) { return D4(w[i - 2], w[i - 1], w[i + 1], w[i + 2], r); };
-    auto dyw = [&](const CT* w, int i, int s) { return D4(w[i - 2 * s], w[i - s], w[i + s], w[i + 2 * s], r); };
-    const CT dtxx = dxw(txx, wx), dtxy_y = dyw(txy, wc, FX), dtxy_x = dxw(txy, wc), dtyy = dyw(tyy, wy, NB);
     const CT dqx = dxw(qx, wx), dqy = dyw(qy, wy, NB);
     CT kv[4];
     kv[0] = -(dmx + dmy);
@@ -816,8 +834,14 @@ hipError_t go2(K kern, int items, size_t lds, int threads, hipStream_t st, const
 hipError_t launch_stage2(const Shape& s, int precision, const StageArgs& a, hipStream_t st) {
   const int n = a.topo.h.n_blocks;
   if (s.nf == 4) {
-    if (precision == 0) return go2(k_stage_ns<double, double>, NPART * n, NsLds<double, double>::bytes, NST, st, a);
-    return go2(k_stage_ns<float, float>, NPART * n, NsLds<float, float>::bytes, NST, st, a);
+    if (precision == 0)
+      return go2(k_stage_ns<double, double, false>, NPART * n, NsLds<double, double, false>::bytes, NST, st, a);
+    // a third workgroup per compute unit pays when there are more than two for each of the 256
+    // (2,944 blocks: 94.5 us against 100; 1,024: 35.2 against 35.9); up to there its barriers
+    // only cost (256 blocks: 11.3 us against 11.0)
+    if (NPART * n > 512)
+      return go2(k_stage_ns<float, float, true>, NPART * n, NsLds<float, float, true>::bytes, NST, st, a);
+    return go2(k_stage_ns<float, float, false>, NPART * n, NsLds<float, float, false>::bytes, NST, st, a);
   }
   if (s.bs == 33) {
     if (precision == 0) return go2(k_stage2<33, 384, double, double>, n, 0, 384, st, a);

@@ -1291,3 +1291,26 @@ def test_init_forest_refusals_leave_the_forest(dim):
     o.refine_all()
     assert_same(s, o, "refinement after refusals")
     s.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("seed,n", [(0, 256), (1, 271)])
+def test_ns_mixed_stage_on_both_sides_of_two_workgroups_a_unit(seed, n):
+    """The mixed Navier-Stokes stage (halves of blocks) up to 512 workgroups and beyond, where
+    the heat fluxes share the stresses' LDS, on graded forests of three levels: bitwise the
+    sub-tiled kernel's results."""
+    cfg = W.C3(jmax=6, form=W.FORM_FUSED, max_blocks=1000, precision=W.MIXED)
+    lv, co = W.random_graded_forest(2, 5, seed, 0.3, 3)
+    assert len(lv) == n
+    out = []
+    for force in (0, 2):
+        s = M.Solver(cfg)
+        s.init_forest(lv, co)
+        s.load_blocks(W.sample(cfg, *s.read_forest()))
+        if force:
+            s.tune(nsub=force)
+        for k in range(2):
+            s.rk4(k * cfg.dt, cfg.dt)
+        out.append(s.read_blocks())
+        s.close()
+    assert np.array_equal(_bits(out[0]), _bits(out[1]))
