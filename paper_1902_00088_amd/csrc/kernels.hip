@@ -1,8 +1,10 @@
-// HIP kernels of the block-multiresolution sweep (gfx950).
+// HIP kernels of the block-multiresolution sweep (gfx950): sub-tiled stages and analysis, the
+// one-launch sweep, the overlapped-tile RK4 step, the plain form, coarsening and read-back.
+// Whole blocks' stages, analysis, refinement and filter are in column3.hip (3D) and plane2.hip
+// (2D), which the dispatch at the end prefers.
 //
-// A workgroup handles one block (or one sub-tile of a block) per iteration of a
-// grid-stride loop, so a launch does not depend on the block count (it is read from
-// the device topology header) and can be replayed from a graph.
+// A workgroup of a stage handles one block (or one sub-tile of a block) per iteration of a
+// loop over a work list.
 //
 // Ghost synchronisation is a single gather into LDS.  The block's neighbour
 // entries (every leaf whose closed region touches the block: coarser leaves first,
@@ -21,7 +23,6 @@
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <mutex>
-
 
 namespace mrb {
 

@@ -1,5 +1,6 @@
-// 2D stage and filter kernels over whole blocks or halves of blocks (gfx950): advection on
-// blocks of 33^2 or 17^2 points, Navier-Stokes (four fields, halo 4) on 33^2.
+// 2D stage, filter, analysis and refinement kernels over whole blocks or halves of blocks
+// (gfx950): advection on blocks of 33^2 or 17^2 points, Navier-Stokes (four fields, halo 4) on
+// 33^2.
 //
 // As in column3.hip, the owner of a tile point (the finest leaf holding it on its own
 // lattice, Sec. 2.2 and Sec. 2.5) only depends on its zone along each axis -- before the
