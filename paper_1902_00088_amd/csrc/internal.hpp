@@ -198,6 +198,13 @@ struct ReadArgs {
   int level;              // 0: per block; L: uniform lattice of level L (no leaf coarser than L)
 };
 
+struct ScatterArgs {
+  Topo topo;
+  const double* src;      // [n][bsz], forest order
+  double* u;
+  int bsz;                // values of a block
+};
+
 struct Shape {
   int dim, bs, hw, nf;
 };
@@ -246,7 +253,7 @@ int mr_threads(const Shape& s, int nsub, int* tpb, int cap);   // workgroup size
 hipError_t launch_refine(const Shape& s, const RefineArgs& a, hipStream_t st);
 hipError_t launch_coarsen(const Shape& s, int grid, const CoarsenArgs& a, hipStream_t st);
 hipError_t launch_read(const Shape& s, int grid, const ReadArgs& a, hipStream_t st);
-hipError_t launch_scatter(const double* src, const int* slots, int n, size_t bsz, double* dst, hipStream_t st);
+hipError_t launch_scatter(const ScatterArgs& a, hipStream_t st);
 // Device-resident topology transitions (topo.hip).  Arenas share the TopoHeader layout;
 // old_* is the current grid, new_* the next one.
 struct DevTopoArgs {

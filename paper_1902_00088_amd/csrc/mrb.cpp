@@ -242,9 +242,8 @@ struct mrb_ctx {
   double* dghost = nullptr;
   double* dscratch = nullptr;
   size_t scratch_cap = 0;
-  int* dslots = nullptr;
 
-  Staging st_topo[2], st_slots;
+  Staging st_topo[2];
   int st_cur = 0;
   int8_t* h_flags = nullptr;   // pinned, mapped
   double* h_maxd = nullptr;    // pinned, mapped
@@ -1942,14 +1941,6 @@ bool check_state(mrb_ctx* c, bool need_data) {
   return true;
 }
 
-}  // namespace
-
-// scatter/gather of whole blocks between a contiguous array and pool slots
-namespace mrb {
-hipError_t launch_scatter(const double* src, const int* slots, int n, size_t bsz, double* dst, hipStream_t st);
-}
-
-namespace {
 
 // One MR step with the refinement, the four stages and the first analysis replayed
 // from a captured graph (launch parameters are fixed; block counts and
@@ -2505,7 +2496,7 @@ mrb_status mrb_create(const mrb_config* cfg, double* u, double* u_new, void* k1,
   const size_t mb = cfg->max_blocks;
   bool ok = dev((void**)&c->dacc, mb * cfg->nfields * 8) && dev((void**)&c->ddone, mb * sizeof(int)) &&
             hipMemset(c->dacc, 0, mb * cfg->nfields * 8) == hipSuccess &&
-            hipMemset(c->ddone, 0, mb * sizeof(int)) == hipSuccess && dev((void**)&c->dslots, mb * sizeof(int));
+            hipMemset(c->ddone, 0, mb * sizeof(int)) == hipSuccess;
   if (ok && cfg->physics == MRB_ADV_SWIRL) {
     const size_t n = (size_t)(1L << cfg->jmax) * (cfg->bs - 1);
     ok = dev((void**)&c->ds2, n * sizeof(double)) && dev((void**)&c->ds, n * sizeof(double));
@@ -2579,7 +2570,7 @@ mrb_status mrb_create(const mrb_config* cfg, double* u, double* u_new, void* k1,
 mrb_status mrb_destroy(mrb_ctx* c) {
   if (!c) return MRB_E_ARG;
   (void)hipStreamSynchronize(c->stream);
-  Staging* sts[] = {&c->st_topo[0], &c->st_topo[1], &c->st_slots};
+  Staging* sts[] = {&c->st_topo[0], &c->st_topo[1]};
   for (Staging* s : sts) release_staging(*s);
   for (auto& t : c->timed) { (void)hipEventDestroy(t.a); (void)hipEventDestroy(t.b); }
   for (auto& g : c->graphs) (void)hipGraphExecDestroy(g.exec);
@@ -2592,7 +2583,7 @@ mrb_status mrb_destroy(mrb_ctx* c) {
     if (e.arena) (void)hipFree(e.arena);
   dev_release(c);
   void* ptrs[] = {c->work_arena, c->dacc, c->ddone,
-                  c->ds2, c->ds, c->dghost, c->dscratch, c->dslots, c->dbar};
+                  c->ds2, c->ds, c->dghost, c->dscratch, c->dbar};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (c->h_flags) (void)hipHostFree(c->h_flags);
@@ -2674,10 +2665,7 @@ mrb_status mrb_load_blocks(mrb_ctx* c, const double* data, int on_device) {
     HIPCHK(c, hipMemcpyAsync(c->dscratch, data, bytes, hipMemcpyHostToDevice, c->stream));
     src = c->dscratch;
   }
-  std::vector<int> slots(n);
-  for (int i = 0; i < n; ++i) slots[i] = c->leaves[i].slot;
-  if ((s = stage_upload(c, c->st_slots, slots.data(), n * sizeof(int), c->dslots))) return s;
-  HIPCHK(c, launch_scatter(src, c->dslots, n, c->bsz, c->u, c->stream));
+  HIPCHK(c, launch_scatter(ScatterArgs{topo(c), src, c->u, (int)c->bsz}, c->stream));
   if (!on_device) HIPCHK(c, hipStreamSynchronize(c->stream));
   c->have_data = true;
   c->have_flags = false;
