@@ -230,8 +230,8 @@ hipError_t launch_mr3(const MrArgs& a, hipStream_t st);
 hipError_t launch_refine3(const RefineArgs& a, hipStream_t st);
 hipError_t launch_mr2(const Shape& s, int tpb, const MrArgs& a, hipStream_t st);
 hipError_t launch_refine2(const Shape& s, const RefineArgs& a, hipStream_t st);
-// 2D stages of whole blocks (halves of them for Navier-Stokes) and the filter (plane2.hip):
-// the stage variant of plane_threads threads
+// 2D stages of whole blocks (halves or thirds of them for Navier-Stokes) and the filter
+// (plane2.hip): the stage variant of zone_threads threads (kNsThreads: of the halves)
 constexpr int kNsThreads = 576;
 hipError_t launch_stage2(const Shape& s, int precision, const StageArgs& a, hipStream_t st);
 hipError_t launch_filter(const FilterArgs& a, hipStream_t st);   // NS shape only

@@ -288,18 +288,18 @@ __global__ void __launch_bounds__(TPB) k_stage2(StageArgs A) {
 }
 
 // ---------------------------------------------------------------------------
-// Navier-Stokes stage (primitive variables rho, u, v, p) of half a block per workgroup
-// (rows 0..16 or 17..32, one node per thread).  The tile is FP64, CT the arithmetic type
+// Navier-Stokes stage (primitive variables rho, u, v, p) of half or a third of a block per
+// workgroup (SY rows, one node per thread).  The tile is FP64, CT the arithmetic type
 // (see ns_fluxes in kernels.hip, whose operations these are, point by point).  p / rho is
 // formed once per tile point (it had cost eight FP64 divisions per flux point), and a
 // node's gradients, stresses and momentum factors pass from its fluxes to its right-hand
 // side in registers.  Bound by vector instructions (4,800 a half block, half of their
 // issue slots), LDS reads (40 us) and memory (260 MB, 50 us) together, overlapped by the two
-// or three workgroups that fit a compute unit's LDS; thirds of blocks are no faster, quarters
-// slower.  2,944 blocks on five levels: 94.5 us a stage mixed (100 with two workgroups a
-// compute unit) against 244 us for whole blocks of 256 threads; 1,024 blocks FP64: 43 against 76 us.
+// to four workgroups that fit a compute unit's LDS.  2,944 blocks on five levels: 89 us a stage
+// mixed against 244 us for whole blocks of 256 threads; 1,024 blocks FP64: 42 against 76 us.
 // ---------------------------------------------------------------------------
-constexpr int NB = 33, NSY = 17, NST = kNsThreads, NPART = (NB + NSY - 1) / NSY;
+constexpr int NB = 33;
+constexpr int ns_parts(int sy) { return (NB + sy - 1) / sy; }
 
 template <typename CT>
 __device__ __forceinline__ CT D4d(double um2, double um1, double up1, double up2, CT r) {
@@ -308,23 +308,23 @@ __device__ __forceinline__ CT D4d(double um2, double um1, double up1, double up2
 }
 
 // SHARE: the coarse lattice lies where the tile comes to lie and the heat fluxes take the place
-// of the normal stresses once these are read, three barriers more; in FP32 a third workgroup
-// fits the compute unit's LDS then
-template <typename KT, typename CT, bool SHARE>
+// of the normal stresses once these are read, three barriers more, for one workgroup more in the
+// compute unit's LDS (thirds of blocks, mixed: 39 KB instead of 53)
+template <typename KT, typename CT, bool SHARE, int SY, int T>
 struct NsLds {
-  using T2 = Tile2<NB, 4, 4, NSY, NST>;
-  static constexpr int FX = NB + 4, FY = NSY + 4;            // flux points -2 .. 34, -2 .. cnt + 1
-  static constexpr int NXX = FX * NSY, NYY = NB * FY, NXY = FX * FY;
+  using T2 = Tile2<NB, 4, 4, SY, T>;
+  static constexpr int FX = NB + 4, FY = SY + 4;            // flux points -2 .. 34, -2 .. cnt + 1
+  static constexpr int NXX = FX * SY, NYY = NB * FY, NXY = FX * FY;
   static constexpr size_t tile = sizeof(double) * T2::TSZ * 5;   // four fields and p / rho
   static constexpr size_t flux = sizeof(CT) * ((SHARE ? 1 : 2) * (NXX + NYY) + NXY), lat = sizeof(double) * 2 * 4 * T2::CSZ;
   static constexpr size_t bytes = tile + (SHARE || flux > lat ? flux : lat);
   static_assert(lat <= tile, "the lattice is dead before the tile (SHARE) or the fluxes are written");
 };
 
-template <typename KT, typename CT, bool SHARE>
-__global__ void __launch_bounds__(NST) k_stage_ns(StageArgs A) {
-  using L = NsLds<KT, CT, SHARE>;
-  using G = Gather2<NB, 4, 4, NSY, NST, double>;
+template <typename KT, typename CT, bool SHARE, int SY, int T>
+__global__ void __launch_bounds__(T) k_stage_ns(StageArgs A) {
+  using L = NsLds<KT, CT, SHARE, SY, T>;
+  using G = Gather2<NB, 4, 4, SY, T, double>;
   using T2 = typename G::T2;
   constexpr int TW = T2::TW, TSZ = T2::TSZ, NP = T2::NP, HW = 4, FX = L::FX;
   __shared__ Rows2<T2::ROWS> zn;
@@ -337,13 +337,13 @@ __global__ void __launch_bounds__(NST) k_stage_ns(StageArgs A) {
   CT* tyy = txx + L::NXX;                            // x 0..32, y -2..18
   CT* qx = SHARE ? txx : tyy + L::NYY;
   CT* qy = SHARE ? tyy : qx + L::NXX;
-  const XcdWork it(NPART * A.topo.h.n_blocks);       // one work item per workgroup
+  const XcdWork it(ns_parts(SY) * A.topo.h.n_blocks);       // one work item per workgroup
   if (!it.ok()) return;
-  const int tid = threadIdx.x, part = it.w % NPART;
-  const int b = A.order ? A.topo.list()[it.w / NPART] : it.w / NPART;
+  const int tid = threadIdx.x, part = it.w % ns_parts(SY);
+  const int b = A.order ? A.topo.list()[it.w / ns_parts(SY)] : it.w / ns_parts(SY);
   const BlockDesc d = A.topo.blk()[b];
-  const int y0 = part * NSY, cnty = min(NSY, NB - y0);
-  row_table<NB, 4, NST>(zn, d, A.topo.nb(b), A.topo.h.nb_stride, y0 - T2::H);
+  const int y0 = part * SY, cnty = min(SY, NB - y0);
+  row_table<NB, 4, T>(zn, d, A.topo.nb(b), A.topo.h.nb_stride, y0 - T2::H);
   const int base = d.slot * 4 * NP;
   {
     G g;
@@ -373,7 +373,7 @@ __global__ void __launch_bounds__(NST) k_stage_ns(StageArgs A) {
   // Stresses and heat flux, each where a derivative along x or y reads it: at the thread's
   // own node, whose velocity gradients, stresses and momentum factors stay in registers for
   // the right-hand side, then at the points beside the region (two per side and row).
-  static_assert(NB * NSY <= NST, "one region node per thread");
+  static_assert(NB * SY <= T, "one region node per thread");
   const int nn = NB * cnty;
   const bool mine = tid < nn;
   const int ly = mine ? tid / NB : 0, lx = mine ? tid - ly * NB : 0;
@@ -397,7 +397,7 @@ __global__ void __launch_bounds__(NST) k_stage_ns(StageArgs A) {
     txy[wc] = sxy;
   }
   // beside the region along x (xs) or y
-  const int sp = NST - 1 - tid, nside = 4 * cnty;    // the last waves have fewer own nodes
+  const int sp = T - 1 - tid, nside = 4 * cnty;    // the last waves have fewer own nodes
   const bool side = sp < nside + 4 * NB, xs = sp < nside;
   const int sk = xs ? sp % 4 : (sp - nside) / NB;
   const int fx = xs ? (sk < 2 ? sk - 2 : NB - 2 + sk) : (sp - nside) % NB;
@@ -474,17 +474,18 @@ __global__ void __launch_bounds__(NST) k_stage_ns(StageArgs A) {
 }
 
 // ---------------------------------------------------------------------------
-// Shock-capturing filter after a time step (formulas at FilterArgs), half a block per
-// workgroup: per axis the pressure sensor of one point more than the region on either side,
-// then the switched second-order fluxes.  2,944 blocks: 58 us (205 MB of block data,
-// 3.5 TB/s) against 149 us for whole blocks of 256 threads, one per compute unit.
+// Shock-capturing filter after a time step (formulas at FilterArgs), half or a third of a
+// block per workgroup: per axis the pressure sensor of one point more than the region on either
+// side, then the switched second-order fluxes.  2,944 blocks: 69 us (205 MB of block data,
+// 3.0 TB/s) against 149 us for whole blocks of 256 threads, one per compute unit.
 // ---------------------------------------------------------------------------
 constexpr int FHW = 3;   // p is read up to 3 beyond the region, the other fields 1
 
+template <int SY, int T>
 struct FilterLds {
-  using T2 = Tile2<NB, 4, FHW, NSY, NST>;
-  static constexpr int SX = (NB + 2) * NSY, SY = NB * (NSY + 2);
-  static constexpr size_t tile = sizeof(double) * 4 * T2::TSZ, sens = sizeof(double) * (SX + SY),
+  using T2 = Tile2<NB, 4, FHW, SY, T>;
+  static constexpr int NX = (NB + 2) * SY, NY = NB * (SY + 2);
+  static constexpr size_t tile = sizeof(double) * 4 * T2::TSZ, sens = sizeof(double) * (NX + NY),
                           lat = sizeof(double) * 2 * 4 * T2::CSZ;
   static constexpr size_t bytes = tile + (sens > lat ? sens : lat);   // (the lattice is dead before the sensors)
 };
@@ -493,8 +494,9 @@ struct FilterValue {
   __device__ __forceinline__ double operator()(double u, int) const { return u; }
 };
 
-__global__ void __launch_bounds__(NST) k_filter2(FilterArgs A) {
-  using G = Gather2<NB, 4, FHW, NSY, NST, double>;
+template <int SY, int T>
+__global__ void __launch_bounds__(T) k_filter2(FilterArgs A) {
+  using G = Gather2<NB, 4, FHW, SY, T, double>;
   using T2 = typename G::T2;
   constexpr int TW = T2::TW, TSZ = T2::TSZ, NP = T2::NP, SXW = NB + 2;
   __shared__ Rows2<T2::ROWS> zn;
@@ -502,13 +504,13 @@ __global__ void __launch_bounds__(NST) k_filter2(FilterArgs A) {
   double* tile = reinterpret_cast<double*>(smem);
   double* carr = tile + 4 * TSZ;
   double* sx = carr;                     // sensor along x at x = -1..33, y = 0..cnt-1
-  double* sy = sx + FilterLds::SX;       // sensor along y at x = 0..32, y = -1..cnt
-  const XcdWork it(NPART * A.topo.h.n_blocks);
+  double* sy = sx + FilterLds<SY, T>::NX;       // sensor along y at x = 0..32, y = -1..cnt
+  const XcdWork it(ns_parts(SY) * A.topo.h.n_blocks);
   if (!it.ok()) return;
-  const int tid = threadIdx.x, part = it.w % NPART, b = it.w / NPART;
+  const int tid = threadIdx.x, part = it.w % ns_parts(SY), b = it.w / ns_parts(SY);
   const BlockDesc d = A.topo.blk()[b];
-  const int y0 = part * NSY, cnty = min(NSY, NB - y0);
-  row_table<NB, 4, NST>(zn, d, A.topo.nb(b), A.topo.h.nb_stride, y0 - T2::H);
+  const int y0 = part * SY, cnty = min(SY, NB - y0);
+  row_table<NB, 4, T>(zn, d, A.topo.nb(b), A.topo.h.nb_stride, y0 - T2::H);
   const int base = d.slot * 4 * NP;
   {
     G g;
@@ -531,7 +533,7 @@ __global__ void __launch_bounds__(NST) k_filter2(FilterArgs A) {
     const double sv = 1.0 - A.rth / r;
     return sv > 0.0 ? sv : 0.0;
   };
-  for (int p = tid; p < SXW * cnty + NB * (cnty + 2); p += NST) {
+  for (int p = tid; p < SXW * cnty + NB * (cnty + 2); p += T) {
     if (p < SXW * cnty) {
       const int y = p / SXW, x = p - y * SXW;
       sx[p] = sens(x - 1 + FHW + TW * (y + FHW), 1);
@@ -541,6 +543,7 @@ __global__ void __launch_bounds__(NST) k_filter2(FilterArgs A) {
     }
   }
   __syncthreads();
+  static_assert(NB * SY <= T, "one node per thread");
   if (tid < NB * cnty) {
     const int y = tid / NB, x = tid - y * NB;
     const double sx0 = sx[(x + 1) + SXW * y], sy0 = sy[x + NB * (y + 1)];
@@ -830,19 +833,27 @@ hipError_t go2(K kern, int items, size_t lds, int threads, hipStream_t st, const
   return hipGetLastError();
 }
 
+template <typename KT, typename CT, bool SHARE, int SY, int T>
+hipError_t go_ns(int n, hipStream_t st, const StageArgs& a) {
+  return go2(k_stage_ns<KT, CT, SHARE, SY, T>, ns_parts(SY) * n, NsLds<KT, CT, SHARE, SY, T>::bytes, T, st, a);
+}
+
 }  // namespace
 
 hipError_t launch_stage2(const Shape& s, int precision, const StageArgs& a, hipStream_t st) {
   const int n = a.topo.h.n_blocks;
   if (s.nf == 4) {
-    if (precision == 0)
-      return go2(k_stage_ns<double, double, false>, NPART * n, NsLds<double, double, false>::bytes, NST, st, a);
-    // a third workgroup per compute unit pays when there are more than two for each of the 256
-    // (2,944 blocks: 94.5 us against 100; 1,024: 35.2 against 35.9); up to there its barriers
-    // only cost (256 blocks: 11.3 us against 11.0)
-    if (NPART * n > 512)
-      return go2(k_stage_ns<float, float, true>, NPART * n, NsLds<float, float, true>::bytes, NST, st, a);
-    return go2(k_stage_ns<float, float, false>, NPART * n, NsLds<float, float, false>::bytes, NST, st, a);
+    // Up to two halves for each of the 256 compute units are one round of workgroups, and their
+    // latency counts; beyond, thirds of blocks leave room for three (FP64) or four (mixed) on a
+    // unit.  2,944 blocks mixed: 88.9 us a stage in thirds against 94.3 in halves (100 without
+    // SHARE); 1,024 blocks FP64: 41.8 against 43.2; 256 blocks mixed: 10.5 us in halves, 10.8 to
+    // 11.4 in thirds, 11.0 against 11.3 with SHARE.
+    if (2 * n > 512) {
+      if (precision == 0) return go_ns<double, double, false, 11, 448>(n, st, a);
+      return go_ns<float, float, true, 11, 512>(n, st, a);
+    }
+    if (precision == 0) return go_ns<double, double, false, 17, kNsThreads>(n, st, a);
+    return go_ns<float, float, false, 17, kNsThreads>(n, st, a);
   }
   if (s.bs == 33) {
     if (precision == 0) return go2(k_stage2<33, 384, double, double>, n, 0, 384, st, a);
@@ -874,8 +885,12 @@ hipError_t launch_refine2(const Shape& s, const RefineArgs& a, hipStream_t st) {
   return go2(k_refine2<17, 1, 320>, n, 0, 320, st, a);
 }
 
+// (halves and thirds as in the stage: 2,944 blocks 70.2 us in halves, 68.7 in thirds; 1,024:
+// 25.9 and 24.7)
 hipError_t launch_filter(const FilterArgs& a, hipStream_t st) {
-  return go2(k_filter2, NPART * a.topo.h.n_blocks, FilterLds::bytes, NST, st, a);
+  const int n = a.topo.h.n_blocks;
+  if (2 * n > 512) return go2(k_filter2<11, 448>, ns_parts(11) * n, FilterLds<11, 448>::bytes, 448, st, a);
+  return go2(k_filter2<17, kNsThreads>, ns_parts(17) * n, FilterLds<17, kNsThreads>::bytes, kNsThreads, st, a);
 }
 
 }  // namespace mrb

@@ -1295,13 +1295,28 @@ def test_init_forest_refusals_leave_the_forest(dim):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("seed,n", [(0, 256), (1, 271)])
-def test_ns_mixed_stage_on_both_sides_of_two_workgroups_a_unit(seed, n):
-    """The mixed Navier-Stokes stage (halves of blocks) up to 512 workgroups and beyond, where
-    the heat fluxes share the stresses' LDS, on graded forests of three levels: bitwise the
-    sub-tiled kernel's results."""
-    cfg = W.C3(jmax=6, form=W.FORM_FUSED, max_blocks=1000, precision=W.MIXED)
+@pytest.mark.parametrize("which", ["C3 mixed", "DSL FP64"])
+def test_ns_stage_on_both_sides_of_two_workgroups_a_unit(seed, n, which):
+    """The Navier-Stokes stage and filter in halves of blocks up to 512 workgroups and in thirds
+    beyond, on graded forests of three levels: mixed bitwise the sub-tiled kernel's results,
+    FP64 with the filter bitwise the oracle's."""
     lv, co = W.random_graded_forest(2, 5, seed, 0.3, 3)
     assert len(lv) == n
+    if which == "DSL FP64":
+        cfg = W.DSL(jmax=6, form=W.FORM_FUSED, max_blocks=1000)
+        s, o = M.Solver(cfg), oracle.Oracle(cfg)
+        o.init_forest(lv, co)
+        s.init_forest(lv, co)
+        data = W.sample(cfg, *s.read_forest())
+        s.load_blocks(data)
+        o.load_blocks(data)
+        for k in range(2):
+            s.rk4(k * cfg.dt, cfg.dt)
+            o.rk4(k * cfg.dt, cfg.dt)
+        assert np.array_equal(_bits(s.read_blocks()), _bits(o.read_blocks()))
+        s.close()
+        return
+    cfg = W.C3(jmax=6, form=W.FORM_FUSED, max_blocks=1000, precision=W.MIXED)
     out = []
     for force in (0, 2):
         s = M.Solver(cfg)
