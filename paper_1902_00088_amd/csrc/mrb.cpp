@@ -212,6 +212,8 @@ struct mrb_ctx {
   TopoHeader arena_hdr{};       // its header (kernels take it by value)
   char* work_arena = nullptr;   // the arena uploads go to (owned)
   size_t arena_cap = 0, arena_bytes = 0;
+  bool topo_ok = true;          // false after an upload that failed: the arena may be gone or
+                                // describe another grid, and the next call uploads again
   // memo of topology transitions on small forests: a refine-all or a coarsening from a
   // state seen before (same leaves, slots, free-list tail and flags) reuses the host
   // plan and a device copy of its packed topology instead of planning and uploading
@@ -671,6 +673,7 @@ mrb_status upload_topo(mrb_ctx* c, const std::vector<BlockDesc>* pblk = nullptr,
                        const std::vector<NbEntry>* pnb = nullptr, const std::vector<RefineDesc>* ref = nullptr,
                        const std::vector<FamilyDesc>* fam = nullptr, const std::vector<int>* smap = nullptr) {
   HostTimer ht(&c->hus_upload);
+  c->topo_ok = false;
   TopoHeader h;
   std::memset(&h, 0, sizeof h);
   h.n_blocks = (int)c->hblk.size();
@@ -705,6 +708,7 @@ mrb_status upload_topo(mrb_ctx* c, const std::vector<BlockDesc>* pblk = nullptr,
     HIPCHK(c, hipStreamSynchronize(c->stream));
     if (c->work_arena) HIPCHK(c, hipFree(c->work_arena));
     c->work_arena = nullptr;
+    c->arena_cap = 0;
     const size_t cap = total + total / 2 + 4096;
     HIPCHK(c, hipMalloc((void**)&c->work_arena, cap));
     c->arena_cap = cap;
@@ -722,6 +726,7 @@ mrb_status upload_topo(mrb_ctx* c, const std::vector<BlockDesc>* pblk = nullptr,
   if (total > S.cap) {
     if (S.h) HIPCHK(c, hipHostFree(S.h));
     S.h = nullptr;
+    S.cap = 0;
     const size_t cap = total + total / 2 + 4096;
     HIPCHK(c, hipHostMalloc(&S.h, cap, hipHostMallocDefault));
     S.cap = cap;
@@ -744,6 +749,7 @@ mrb_status upload_topo(mrb_ctx* c, const std::vector<BlockDesc>* pblk = nullptr,
   HIPCHK(c, hipMemcpyAsync(c->arena, S.h, total, hipMemcpyHostToDevice, c->stream));
   HIPCHK(c, hipEventRecord(S.ev, c->stream));
   S.pending = true;
+  c->topo_ok = true;
   return MRB_OK;
 }
 
@@ -1938,9 +1944,13 @@ mrb_status ensure_scratch(mrb_ctx* c, size_t bytes) {
 bool check_state(mrb_ctx* c, bool need_data) {
   if (!c->have_forest) { c->err = "no forest (call mrb_init_forest first)"; return false; }
   if (need_data && !c->have_data) { c->err = "no block data (call mrb_load_blocks first)"; return false; }
+  if (!c->topo_ok) {   // an earlier upload failed: the kernels must not read what it left
+    c->pending_ref = 0;
+    c->hcount_ref_zero = true;
+    if (upload_topo(c)) return false;
+  }
   return true;
 }
-
 
 // One MR step with the refinement, the four stages and the first analysis replayed
 // from a captured graph (launch parameters are fixed; block counts and
