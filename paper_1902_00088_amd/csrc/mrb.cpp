@@ -823,7 +823,13 @@ mrb_status memo_record(mrb_ctx* c, int kind, std::vector<int>& material, size_t 
     HIPCHK(c, hipFree(e->arena));
     e->arena = nullptr;
   }
-  if (!e->arena) HIPCHK(c, hipMalloc((void**)&e->arena, c->arena_bytes));
+  if (!e->arena && hipMalloc((void**)&e->arena, c->arena_bytes) != hipSuccess) {
+    // no memory for the device copy: the transition stands, it is just not remembered (and
+    // neither is the one this entry held)
+    (void)hipGetLastError();
+    *e = mrb_ctx::Memo{};
+    return MRB_OK;
+  }
   e->arena_bytes = c->arena_bytes;
   e->hdr = c->arena_hdr;
   e->kind = kind;

@@ -47,7 +47,7 @@ bool in_live(const void* p, size_t n) {
   return false;
 }
 
-long scatter_faults = 0;
+long scatter_faults = 0, null_topologies = 0;
 
 void scatter(const mrb::ScatterArgs& a) {
   const mrb::BlockDesc* d = (const mrb::BlockDesc*)(a.topo.base + a.topo.h.off_blk);
@@ -68,6 +68,7 @@ void host_fail_allocation(int n) { fail_in = n; }   // the n-th allocation from 
 void host_compute_units(int n) { units = n; }
 void host_run_copies(int on) { run_copies = on; }
 long host_scatter_faults() { return scatter_faults; }   // block copies that read freed memory
+long host_null_topologies() { return null_topologies; }   // refinements without a topology buffer
 int host_launches() { return (int)launches.size(); }
 const char* host_launch(int i, unsigned long long* grid, unsigned long long* threads) {
   *grid = launches[i].grid;
@@ -101,6 +102,7 @@ hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t, h
   launches.push_back(Launch{names[f], g.x, b.x});
   // a launch holds fewer than 2^32 work items
   if ((unsigned long long)g.x * b.x > 0xffffffffull) return hipErrorInvalidConfiguration;
+  if (names[f].find("k_refine") != std::string::npos && !((const mrb::RefineArgs*)args[0])->topo.base) ++null_topologies;
   if (run_copies && names[f].find("k_scatter") != std::string::npos) scatter(*(const mrb::ScatterArgs*)args[0]);
   return hipSuccess;
 }

@@ -16,7 +16,7 @@ sys.path.insert(0, {root!r})
 import numpy as np
 host = ctypes.CDLL({so!r}, mode=ctypes.RTLD_GLOBAL)   # before the library that needs a HIP runtime
 host.host_launch.restype = ctypes.c_char_p
-host.host_scatter_faults.restype = ctypes.c_long
+host.host_scatter_faults.restype = host.host_null_topologies.restype = ctypes.c_long
 
 
 class _Array:

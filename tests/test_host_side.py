@@ -42,3 +42,43 @@ while True:
     nth += 1
 assert nth > 1
 ''')
+
+
+def test_transition_without_memory_to_remember_it(tmp_path):
+    """A refinement or coarsening whose device copy for later replays cannot be allocated takes
+    place all the same (kernel launched, forest changed), also where the copy would take the
+    place of an older, smaller one, which is then forgotten."""
+    run(tmp_path, '''
+cfg = W.C1(jmax=5, form=W.FORM_FUSED)
+lv, co = W.uniform_forest(cfg, 1)
+
+
+def marked(s, k):
+    mask = np.zeros(s.num_blocks(), np.int8)
+    mask[k] = 1
+    s.refine_marked(mask)
+    assert host.host_null_topologies() == 0
+
+
+for nth in range(1, 8):                  # every allocation of a refinement of a larger forest
+    s = solver(cfg, lv, co)
+    for n in range(12):                  # more transitions than are remembered
+        marked(s, n % 4)
+    s.init_forest(*W.uniform_forest(cfg, 3))
+    s.load_blocks(np.zeros((64, 1, cfg.npts)))
+    launches()
+    host.host_fail_allocation(nth)
+    try:
+        s.refine_all()
+    except M.MrbError as e:
+        assert e.code == -5 and s.num_blocks() == 64 and not any("refine" in k[0] for k in launches())
+    else:
+        assert s.num_blocks() == 256 and any("refine" in k[0] for k in launches())
+    host.host_fail_allocation(0)
+    for first in range(4):               # what an entry without a copy held is planned anew
+        s.init_forest(lv, co)
+        s.load_blocks(np.zeros((4, 1, cfg.npts)))
+        for n in range(12):
+            marked(s, (first + n) % 4)
+    s.close()
+''')
