@@ -1941,6 +1941,7 @@ mrb_status ensure_scratch(mrb_ctx* c, size_t bytes) {
     HIPCHK(c, hipStreamSynchronize(c->stream));
     HIPCHK(c, hipFree(c->dscratch));
     c->dscratch = nullptr;
+    c->scratch_cap = 0;
   }
   HIPCHK(c, hipMalloc(&c->dscratch, bytes));
   c->scratch_cap = bytes;

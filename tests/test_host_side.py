@@ -82,3 +82,23 @@ for nth in range(1, 8):                  # every allocation of a refinement of a
             marked(s, (first + n) % 4)
     s.close()
 ''')
+
+
+def test_load_after_one_whose_staging_could_not_grow(tmp_path):
+    """A load from host memory whose device staging cannot grow is refused; a smaller one after
+    it gets a buffer of its own."""
+    run(tmp_path, '''
+cfg = W.C1(jmax=4, form=W.FORM_FUSED)
+s = solver(cfg, *W.uniform_forest(cfg, 1))
+s.init_forest(*W.uniform_forest(cfg, 3))
+host.host_fail_allocation(1)
+try:
+    s.load_blocks(np.zeros((64, 1, cfg.npts)))
+    assert False
+except M.MrbError as e:
+    assert e.code == -5
+s.init_forest(*W.uniform_forest(cfg, 1))
+data = np.random.default_rng(0).random((4, 1, cfg.npts))
+s.load_blocks(data)
+assert np.array_equal(s.u.a.reshape(-1, cfg.npts)[:4], data[:, 0])
+''')
