@@ -3421,6 +3421,7 @@ mrb_status mlp_ready(mrb_ctx* c) {
 mrb_status mlp_workspace(mrb_ctx* c, int n) {
   if (n <= c->mlp_cap) return MRB_OK;
   HIPCHK(c, hipStreamSynchronize(c->stream));
+  c->mlp_cap = 0;
   float** fl[] = {&c->mx, &c->mxn, &c->ma1, &c->ma2, &c->mlog, &c->mloss, &c->mdl, &c->mdz1, &c->mdz2, &c->mpmax};
   for (float** p : fl)
     if (*p) { (void)hipFree(*p); *p = nullptr; }

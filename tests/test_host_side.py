@@ -102,3 +102,31 @@ data = np.random.default_rng(0).random((4, 1, cfg.npts))
 s.load_blocks(data)
 assert np.array_equal(s.u.a.reshape(-1, cfg.npts)[:4], data[:, 0])
 ''')
+
+
+def test_predictor_batch_after_one_without_memory(tmp_path):
+    """A batch whose workspace cannot grow (any of its buffers) is refused; a smaller one after
+    it gets buffers of its own."""
+    run(tmp_path, '''
+cfg = W.C1(jmax=2, form=W.FORM_FUSED)
+x = np.ones((64, 64), np.float32)
+y, cw = np.zeros(64, np.int8), np.ones(3, np.float32)
+nth = 1
+while True:
+    s = solver(cfg, *W.uniform_forest(cfg, 1))
+    s.mlp_init(W.mlp_init_params(64, 1), np.zeros(1, np.float32), np.ones(1, np.float32))
+    s.mlp_grad(x[:16], y[:16], cw)
+    host.host_fail_allocation(nth)
+    try:
+        s.mlp_grad(x, y, cw)
+        failed = False
+    except M.MrbError as e:
+        failed = True
+        assert e.code == -5
+    host.host_fail_allocation(0)
+    s.mlp_grad(x[:16], y[:16], cw)
+    if not failed:
+        break
+    nth += 1
+assert nth == 13
+''')
