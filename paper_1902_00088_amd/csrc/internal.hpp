@@ -133,6 +133,7 @@ struct SweepArgs {
 // are all on one level): u over the region plus 4 halo widths, every stage in LDS.
 struct Rk4tArgs {
   Topo topo;
+  int b0, nb;             // blocks of this launch (set by launch_rk4t)
   const double* u;
   double* unew;
   double alpha[4];        // y_s = u + alpha_s k_{s-1}

@@ -1018,12 +1018,11 @@ __global__ void __launch_bounds__(TPB, TPB >= 512 ? 4 : 2) k_rk4t(Rk4tArgs A) {
   __shared__ int tab[9];                            // same-level holder by direction
   __shared__ double sw[4 * TW];
   __shared__ double red[2 * (TPB / 64)];
-  const int nblk = A.topo.h.n_blocks;
   const BlockDesc* blk = A.topo.blk();
   const int tid = threadIdx.x;
-  const XcdWork it(nblk * NSUBT);   // one work item per workgroup
+  const XcdWork it(A.nb * NSUBT);   // one work item per workgroup
   if (!it.ok()) return;
-  const int b = it.w / NSUBT;
+  const int b = A.b0 + it.w / NSUBT;
   // everything the work item's addresses depend on, requested at once: the block, its
   // (or, with REF, its parent's) entry row up to the row stride -- entries past the
   // count are ignored --, the speculation map and the refinement plan's child slot
@@ -1844,10 +1843,9 @@ static hipError_t rk4t_go(bool ana, bool ref, bool ma, int tpb, int grid, const 
   return go(k_rk4t<B, NS, TT, KT, false, T>, grid, TileGeo<B, NS, false>::template lds<TT>(), st, a, T);
 }
 
-hipError_t launch_rk4t(const Shape& s, int precision, int nsub, bool analysis, bool refine, bool mothers, int tpb,
-                       const Rk4tArgs& a, hipStream_t st) {
-  if (s.dim != 2 || s.hw != 2 || s.nf != 1) return hipErrorInvalidValue;
-  const int grid = a.topo.h.n_blocks * nsub * nsub;   // one workgroup per work item
+static hipError_t rk4t_launch(const Shape& s, int precision, int nsub, bool analysis, bool refine, bool mothers, int tpb,
+                              const Rk4tArgs& a, hipStream_t st) {
+  const int grid = a.nb * nsub * nsub;   // one workgroup per work item
 #define X(B, P, NS)                                                                                              \
   if (s.bs == B && precision == P && nsub == NS) {                                                              \
     if constexpr (P == 0) return rk4t_go<B, NS, double, double>(analysis, refine, mothers, tpb, grid, a, st);   \
@@ -1856,6 +1854,21 @@ hipError_t launch_rk4t(const Shape& s, int precision, int nsub, bool analysis, b
   MRB_RK4T_VARIANTS(X)
 #undef X
   return hipErrorInvalidValue;
+}
+
+hipError_t launch_rk4t(const Shape& s, int precision, int nsub, bool analysis, bool refine, bool mothers, int tpb,
+                       const Rk4tArgs& args, hipStream_t st) {
+  if (s.dim != 2 || s.hw != 2 || s.nf != 1) return hipErrorInvalidValue;
+  // A launch holds fewer than 2^32 threads: 2^20 workgroups of up to 1,024.  Forests of more
+  // (4 x 4 sub-tiles of 65,536 blocks on) take several launches, each over a range of blocks.
+  const int n = args.topo.h.n_blocks, most = (1 << 20) / (nsub * nsub);
+  Rk4tArgs a = args;
+  hipError_t e = hipSuccess;
+  for (a.b0 = 0; a.b0 < n && e == hipSuccess; a.b0 += a.nb) {
+    a.nb = std::min(most, n - a.b0);
+    e = rk4t_launch(s, precision, nsub, analysis, refine, mothers, tpb, a, st);
+  }
+  return e;
 }
 
 int rk4t_variants(const Shape& s, int precision, int* nsub, int cap) {

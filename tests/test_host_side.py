@@ -130,3 +130,55 @@ while True:
     nth += 1
 assert nth == 13
 ''')
+
+
+def test_launches_of_the_largest_forests(tmp_path):
+    """No launch holds 2^32 threads or more, and the launches of a call have a workgroup for each
+    of its work items, on 2^20 blocks of 33^2 (46 GB of pool in FP64): the tile step on whole
+    blocks, 2 x 2 and 4 x 4 sub-tiles, plain and with the refinement and the analysis folded in
+    (1,024 threads), the stage launches, the analysis, and the autotuner over all of them."""
+    run(tmp_path, '''
+cfg = W.C2(jmax=10, form=W.FORM_FUSED).replace(max_blocks=(1 << 20) + (1 << 18))
+forest = {}
+for l in (9, 10):
+    lv, co = W.uniform_forest(cfg, l)
+    order = morton(co)
+    forest[l] = lv, co[order]
+s = pool_free_solver(cfg, *forest[10])
+s.set_topology(0)
+
+
+def load(l):
+    s.init_forest(*forest[l])
+    s._chk(M.lib().mrb_load_blocks(s.h, 8, 1))
+    launches()
+
+
+def check(items, kernel, calls=1):
+    got = launches()
+    assert all(g * t < 2 ** 32 for _, g, t in got), got
+    mine = [g for name, g, t in got if kernel in name]
+    assert sum(mine) >= calls * items and len(mine) >= calls, (kernel, items, got)
+
+
+n = 1 << 20
+s.set_sweep(3)
+for nsub, tpb in ((1, 1024), (2, 1024), (4, 256)):
+    s.tune(nsub=nsub, reps=-tpb)
+    load(10)
+    s.rk4(0.0, cfg.dt)
+    check(n * nsub * nsub, "k_rk4t")
+    load(9)
+    s.step(0.0, cfg.dt)                      # level 9 refined to level 10 inside the tile launch
+    check(n * nsub * nsub, "k_rk4t")
+load(10)
+s.set_sweep(0)
+s.tune()
+s.rk4(0.0, cfg.dt)
+check(n, "k_stage", 4)
+s.mr_pass()
+check(n, "k_mr")
+s.set_sweep(2)
+s.tune(reps=1)
+check(n, "k_rk4t")
+''')
