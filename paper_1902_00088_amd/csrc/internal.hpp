@@ -217,7 +217,7 @@ struct Variant {
 };
 
 // Launchers (kernels.hip).  grid = number of workgroups (grid-stride loops inside).
-hipError_t launch_stage(const Shape& s, int precision, Variant v, int grid, const StageArgs& a, hipStream_t st);
+hipError_t launch_stage(const Shape& s, int precision, Variant v, int grid, int ncu, const StageArgs& a, hipStream_t st);
 // Whole-sweep kernel, cooperative launch of at most one workgroup per compute unit
 // (and at most `max_grid`); *grid_out gets the count.  hipErrorInvalidValue if the
 // variant is not compiled.
@@ -234,8 +234,9 @@ hipError_t launch_refine2(const Shape& s, const RefineArgs& a, hipStream_t st);
 // 2D stages of whole blocks (halves or thirds of them for Navier-Stokes) and the filter
 // (plane2.hip): the stage variant of zone_threads threads (kNsThreads: of the halves)
 constexpr int kNsThreads = 576;
-hipError_t launch_stage2(const Shape& s, int precision, const StageArgs& a, hipStream_t st);
-hipError_t launch_filter(const FilterArgs& a, hipStream_t st);   // NS shape only
+// ncu: the device's compute units
+hipError_t launch_stage2(const Shape& s, int precision, int ncu, const StageArgs& a, hipStream_t st);
+hipError_t launch_filter(int ncu, const FilterArgs& a, hipStream_t st);   // NS shape only
 // threads of the zone-owner stage kernel of a shape (column3.hip, plane2.hip)
 inline int zone_threads(const Shape& s) {
   return s.dim == 3 ? kColumnThreads : (s.nf == 4 ? kNsThreads : (s.bs == 33 ? 384 : 448));

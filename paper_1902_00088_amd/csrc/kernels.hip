@@ -1788,9 +1788,9 @@ int stage_threads(const Shape& s, int precision, int nsub, int* tpb, int cap) {
   return n;
 }
 
-hipError_t launch_stage(const Shape& s, int precision, Variant v, int grid, const StageArgs& a, hipStream_t st) {
+hipError_t launch_stage(const Shape& s, int precision, Variant v, int grid, int ncu, const StageArgs& a, hipStream_t st) {
   if (v.nsub == 1 && v.tpb == zone_threads(s))
-    return s.dim == 3 ? launch_stage3(precision, a, st) : launch_stage2(s, precision, a, st);
+    return s.dim == 3 ? launch_stage3(precision, a, st) : launch_stage2(s, precision, ncu, a, st);
 #define X(D, B, W, F, P, NS, T)                                                                  \
   if (s.dim == D && s.bs == B && s.hw == W && s.nf == F && precision == P && v.nsub == NS &&     \
       v.tpb == T)                                                                                \

@@ -956,7 +956,7 @@ mrb_status run_stage(mrb_ctx* c, int s, const StageArgs& a0, bool fixed_grid = f
   for (int d = 0; d < c->cfg.dim; ++d) work *= v.nsub;
   TimeScope ts(c, T_STAGE, (double)n * c->bsz * stage_bytes(c, s), 1, time_it);
   HIPCHK(c, launch_stage(c->shape, c->cfg.precision, v,
-                         fixed_grid ? c->grid : grid_for(c, work), a,
+                         fixed_grid ? c->grid : grid_for(c, work), c->ncu, a,
                          c->stream));
   return MRB_OK;
 }
@@ -1122,7 +1122,7 @@ mrb_status do_filter(mrb_ctx* c) {
   FilterArgs a{topo(c), c->u, c->unew, c->cfg.phys[3]};
   {
     TimeScope ts(c, T_FILTER, (double)n * c->bsz * 16.0);
-    HIPCHK(c, launch_filter(a, c->stream));
+    HIPCHK(c, launch_filter(c->ncu, a, c->stream));
   }
   std::swap(c->u, c->unew);
   return MRB_OK;

@@ -840,15 +840,15 @@ hipError_t go_ns(int n, hipStream_t st, const StageArgs& a) {
 
 }  // namespace
 
-hipError_t launch_stage2(const Shape& s, int precision, const StageArgs& a, hipStream_t st) {
+hipError_t launch_stage2(const Shape& s, int precision, int ncu, const StageArgs& a, hipStream_t st) {
   const int n = a.topo.h.n_blocks;
   if (s.nf == 4) {
-    // Up to two halves for each of the 256 compute units are one round of workgroups, and their
-    // latency counts; beyond, thirds of blocks leave room for three (FP64) or four (mixed) on a
+    // Up to two halves for each of the device's compute units are one round of workgroups, and
+    // their latency counts; beyond (256 blocks on the MI355X), thirds of blocks leave room for three (FP64) or four (mixed) on a
     // unit.  2,944 blocks mixed: 88.9 us a stage in thirds against 94.3 in halves (100 without
     // SHARE); 1,024 blocks FP64: 41.8 against 43.2; 256 blocks mixed: 10.5 us in halves, 10.8 to
     // 11.4 in thirds, 11.0 against 11.3 with SHARE.
-    if (2 * n > 512) {
+    if (n > ncu) {
       if (precision == 0) return go_ns<double, double, false, 11, 448>(n, st, a);
       return go_ns<float, float, true, 11, 512>(n, st, a);
     }
@@ -887,9 +887,9 @@ hipError_t launch_refine2(const Shape& s, const RefineArgs& a, hipStream_t st) {
 
 // (halves and thirds as in the stage: 2,944 blocks 70.2 us in halves, 68.7 in thirds; 1,024:
 // 25.9 and 24.7)
-hipError_t launch_filter(const FilterArgs& a, hipStream_t st) {
+hipError_t launch_filter(int ncu, const FilterArgs& a, hipStream_t st) {
   const int n = a.topo.h.n_blocks;
-  if (2 * n > 512) return go2(k_filter2<11, 448>, ns_parts(11) * n, FilterLds<11, 448>::bytes, 448, st, a);
+  if (n > ncu) return go2(k_filter2<11, 448>, ns_parts(11) * n, FilterLds<11, 448>::bytes, 448, st, a);
   return go2(k_filter2<17, kNsThreads>, ns_parts(17) * n, FilterLds<17, kNsThreads>::bytes, kNsThreads, st, a);
 }
 

@@ -182,3 +182,27 @@ s.set_sweep(2)
 s.tune(reps=1)
 check(n, "k_rk4t")
 ''')
+
+
+@pytest.mark.parametrize("units,level,last", [(32, 2, 5), (256, 4, 0)])
+def test_navier_stokes_split_goes_by_the_devices_compute_units(tmp_path, units, level, last):
+    """The Navier-Stokes stage and filter take halves of blocks up to a block per compute unit of
+    the device at hand and thirds beyond, in both precisions: uniform forests with `last` or
+    more of their blocks refined, 31 and 34 blocks on 32 units, 256 and 259 on 256."""
+    run(tmp_path, f'''
+host.host_compute_units({units})
+for precision in (W.FP64, W.MIXED):
+    cfg = W.DSL(jmax=6, form=W.FORM_FUSED, precision=precision).replace(max_blocks=2000)
+    for refined, parts in (({last}, 2), ({last} + 1, 3)):
+        lv, co = W.uniform_forest(cfg, {level})
+        kids = np.concatenate([2 * co[:refined] + np.array([i, j]) for i in (0, 1) for j in (0, 1)])
+        lv = np.r_[lv[refined:], np.full(len(kids), {level} + 1, np.int8)]
+        co = np.r_[co[refined:], kids.astype(np.int32)]
+        s = pool_free_solver(cfg, lv, co)
+        s.rk4(0.0, cfg.dt)
+        got = [(name, g) for name, g, t in launches()]
+        want = (parts * len(lv) + 7) // 8 * 8
+        assert [g for name, g in got if "k_stage_ns" in name] == [want] * 4, (len(lv), got)
+        assert [g for name, g in got if "k_filter2" in name] == [want], (len(lv), got)
+        s.close()
+''')
