@@ -77,9 +77,10 @@ def traffic_key(wl, form, kind):
 
 
 def tkey(form):
-    """Key suffix of the counter summary for the stage kernel's threads per workgroup."""
-    t = form.get("stage_threads") or 256
-    return "" if t == 256 else f" t{t}"
+    """Key suffix of the counter summary for the stage kernel: its threads per workgroup, and
+    its workgroups per block where it splits blocks by itself."""
+    t, p = form.get("stage_threads") or 256, form.get("stage_parts") or 1
+    return ("" if t == 256 else f" t{t}") + ("" if p == 1 else f" p{p}")
 
 
 def run_form(M, W, torch, cfg, steps, warmup, tune=False):
@@ -118,6 +119,11 @@ def run_form(M, W, torch, cfg, steps, warmup, tune=False):
     t1 = time.perf_counter()
     st = s.stats()
     tiles = st["stage_tiles"]
+    # workgroups per block and threads of the stage launches that ran (a tiling's own sub-tiles
+    # aside); the grid left over after the steps may take others
+    parts, threads = st["stage_ran"] if st["stage_ran"][1] else (st["stage_parts"], st["stage_threads"])
+    if tiles > 1:
+        parts = 1
     host_us = {k: (v - st0["host_us"][k]) / steps for k, v in st["host_us"].items()}
     bu = st["block_updates"] - b0
     wall = t1 - t0
@@ -142,7 +148,8 @@ def run_form(M, W, torch, cfg, steps, warmup, tune=False):
         "kernels": kst,
         "host_us_per_step": host_us,
         "stage_tiles": tiles,
-        "stage_threads": st.get("stage_threads"),
+        "stage_threads": threads,
+        "stage_parts": parts,
         "sweep_launch": st.get("sweep_launch"),
         "rk4_tile": {"tiles": st.get("rk4_tile_tiles"), "analysis_folded": st.get("rk4_tile_analysis"),
                      "refine_folded": st.get("rk4_tile_refine"), "mothers_folded": st.get("rk4_tile_mothers")},

@@ -237,10 +237,27 @@ constexpr int kNsThreads = 576;
 // ncu: the device's compute units
 hipError_t launch_stage2(const Shape& s, int precision, int ncu, const StageArgs& a, hipStream_t st);
 hipError_t launch_filter(int ncu, const FilterArgs& a, hipStream_t st);   // NS shape only
-// threads of the zone-owner stage kernel of a shape (column3.hip, plane2.hip)
+// threads by which a tuning names the zone-owner stage kernel of a shape (column3.hip, plane2.hip)
 inline int zone_threads(const Shape& s) {
   return s.dim == 3 ? kColumnThreads : (s.nf == 4 ? kNsThreads : (s.bs == 33 ? 384 : 448));
 }
+// Workgroups per block and threads of its launch over n blocks.  Navier-Stokes: up to two halves
+// for each of the device's compute units are one round of workgroups, and their latency counts;
+// beyond (256 blocks on the MI355X), thirds of blocks leave room for three (FP64) or four (mixed)
+// on a unit.  2,944 blocks mixed: 88.9 us a stage in thirds against 94.3 in halves (100 without
+// SHARE); 1,024 blocks FP64: 41.8 against 43.2; 256 blocks mixed: 10.5 us in halves, 10.8 to
+// 11.4 in thirds, 11.0 against 11.3 with SHARE.
+struct ZoneForm {
+  int parts, threads;
+};
+constexpr int kNsThirds = 448, kNsThirdsMixed = 512;
+inline ZoneForm zone_form(const Shape& s, int precision, int n, int ncu) {
+  if (s.nf != 4) return ZoneForm{1, zone_threads(s)};
+  if (n <= ncu) return ZoneForm{2, kNsThreads};
+  return ZoneForm{3, precision == 0 ? kNsThirds : kNsThirdsMixed};
+}
+// threads of the analysis of whole blocks where `asked` are chosen
+inline int mr_workgroup(const Shape& s, int asked) { return s.bs == 17 ? 320 : asked; }
 hipError_t launch_plain(const Shape& s, int grid, const StageArgs& a, hipStream_t st);  // ghost + RHS kernels
 // overlapped-tile RK4 step; hipErrorInvalidValue if the shape has no such kernel
 // (threads per workgroup: 256; with the analysis on whole blocks also 512 or 1024;

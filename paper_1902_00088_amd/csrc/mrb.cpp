@@ -293,6 +293,7 @@ struct mrb_ctx {
   int tpb = 256;               // stage threads per workgroup (for the tuned nsub)
   int nsub_mr = -1;            // analysis sub-tiles per axis (-1 = whole blocks, measured best)
   int tpb_mr = 256;            // analysis threads per workgroup for whole blocks (tuned)
+  ZoneForm stage_ran{0, 0};    // workgroups per block and threads of the last stage launch
   int order = 0;               // stage processing order: 0 forest (Morton), 1 level-sorted
   std::string tune_log;
   // captured step graphs (refine, four stages, first analysis), keyed by launch parameters
@@ -923,6 +924,14 @@ Variant pick_stage(const mrb_ctx* c) {
   return Variant{nsub, pick_tpb(c, nsub)};
 }
 
+// workgroups per block and threads of a stage launch of variant v over n blocks
+ZoneForm stage_form(const mrb_ctx* c, Variant v, int n) {
+  if (v.nsub == 1 && v.tpb == zone_threads(c->shape)) return zone_form(c->shape, c->cfg.precision, n, c->ncu);
+  int parts = 1;
+  for (int a = 0; a < c->cfg.dim; ++a) parts *= v.nsub;
+  return ZoneForm{parts, v.tpb};
+}
+
 // threads per workgroup of the analysis kernel: the tuned choice for whole blocks
 int mr_tpb(const mrb_ctx* c, int nsub) { return nsub == 1 ? c->tpb_mr : 256; }
 
@@ -954,6 +963,7 @@ mrb_status run_stage(mrb_ctx* c, int s, const StageArgs& a0, bool fixed_grid = f
   const Variant v = pick_stage(c);
   long work = n;
   for (int d = 0; d < c->cfg.dim; ++d) work *= v.nsub;
+  c->stage_ran = stage_form(c, v, n);
   TimeScope ts(c, T_STAGE, (double)n * c->bsz * stage_bytes(c, s), 1, time_it);
   HIPCHK(c, launch_stage(c->shape, c->cfg.precision, v,
                          fixed_grid ? c->grid : grid_for(c, work), c->ncu, a,
@@ -2935,17 +2945,20 @@ mrb_status mrb_stats(mrb_ctx* c, char* json, int cap) {
     kern += buf;
   }
   kern += "}";
+  // (the stage launch that the current grid would take, and the last one there was)
+  const Variant v = c->have_forest && c->cfg.form == MRB_FORM_FUSED ? pick_stage(c) : Variant{1, 256};
+  const ZoneForm f = stage_form(c, v, (int)nblk(c));
   int w = std::snprintf(json, cap,
                 "{\"blocks\": %zu, \"steps\": %ld, \"rk4\": %ld, \"block_updates\": %ld, \"mr_passes\": %ld, "
                 "\"families_coarsened\": %ld, \"blocks_refined\": %ld, \"free_slots\": %zu, \"grid\": %d, "
-                "\"stage_tiles\": %d, \"stage_threads\": %d, \"stage_order\": \"%s\", \"analysis_threads\": %d, \"graph_launches\": %ld, \"graph_mode\": %d, \"graph_in_use\": %d, \"memo_hits\": %ld, \"spec_hits\": %ld, \"spec_misses\": %ld, \"queued_steps\": %ld, \"queued_taken_back\": %ld, \"sweep_launch\": \"%s\", \"rk4_tile_tiles\": %d, \"rk4_tile_tuned\": %d, \"rk4_tile_analysis\": [%d, %d], \"rk4_tile_refine\": [%d, %d, %d], \"rk4_tile_mothers\": [%d, %d], \"sweep_grid\": %d, \"topology\": \"%s\", \"topology_mode\": %d, \"device_topology\": {\"steps\": %ld, \"passes\": %ld, \"pushes\": %ld, \"pulls\": %ld}, \"host_us\": {\"refine_plan\": %.1f, "
+                "\"stage_tiles\": %d, \"stage_threads\": %d, \"stage_parts\": %d, \"stage_ran\": [%d, %d], \"stage_order\": \"%s\", \"analysis_threads\": %d, \"analysis_workgroup\": %d, \"graph_launches\": %ld, \"graph_mode\": %d, \"graph_in_use\": %d, \"memo_hits\": %ld, \"spec_hits\": %ld, \"spec_misses\": %ld, \"queued_steps\": %ld, \"queued_taken_back\": %ld, \"sweep_launch\": \"%s\", \"rk4_tile_tiles\": %d, \"rk4_tile_tuned\": %d, \"rk4_tile_analysis\": [%d, %d], \"rk4_tile_refine\": [%d, %d, %d], \"rk4_tile_mothers\": [%d, %d], \"sweep_grid\": %d, \"topology\": \"%s\", \"topology_mode\": %d, \"device_topology\": {\"steps\": %ld, \"passes\": %ld, \"pushes\": %ld, \"pulls\": %ld}, \"host_us\": {\"refine_plan\": %.1f, "
                 "\"coarsen_plan\": %.1f, \"upload\": %.1f, \"wait\": %.1f, \"graph_launch\": %.1f, \"plan_ordering\": %.1f, "
                 "\"plan_entries\": %.1f, \"plan_entries_per_block\": %.1f, \"plan_fixed_point\": %.1f}, "
                 "\"tune_ms\": {%s}, \"kernels\": %s}",
                 nblk(c), c->n_steps, c->n_rk4, c->n_block_updates, c->n_mr, c->n_fam, c->n_refined,
-                c->dev.active ? (size_t)c->dev.top : c->free_slots.size(), c->grid, c->have_forest && c->cfg.form == MRB_FORM_FUSED ? pick_stage(c).nsub : 1,
-                c->have_forest && c->cfg.form == MRB_FORM_FUSED ? pick_stage(c).tpb : 256,
+                c->dev.active ? (size_t)c->dev.top : c->free_slots.size(), c->grid, v.nsub, f.threads, f.parts, c->stage_ran.parts, c->stage_ran.threads,
                 c->order ? "level-sorted" : "forest", c->tpb_mr,
+                c->cfg.form == MRB_FORM_FUSED && pick_mr(c) > 1 ? 256 : mr_workgroup(c->shape, c->tpb_mr),
                 c->n_graph_launches, c->graph_mode, c->use_graph ? 1 : 0, c->memo_hits, c->spec_hits, c->spec_misses, c->n_queued, c->n_taken_back,
                 c->have_forest && rk4t_pick(c) > 0 ? "rk4_tile" : (sweep_in_one(c) ? "one" : "four"), c->rk4t_nsub,
                 c->rk4t_tuned ? 1 : 0, c->ana_nsub, c->ana_tpb, c->ref_fold, c->ref_nsub, c->ref_tpb, c->ma_nsub, c->ma_tpb, c->sweep_grid, c->dev.active ? "device" : "host",
@@ -3054,9 +3067,12 @@ mrb_status mrb_tune(mrb_ctx* c, int nsub, int reps, double dt, int* chosen) {
       }
     size_t bi = 0;
     for (size_t i = 0; i < cand.size(); ++i) {
-      // keys: sub-tiles per axis, "t<threads>" unless 256, "L" for the level-sorted order
-      char buf[64], tp[16] = "";
-      if (cand[i].tpb != 256) std::snprintf(tp, sizeof tp, "t%d", cand[i].tpb);
+        // keys: sub-tiles per axis, "t<threads>" unless 256, "p<workgroups per block>" of a
+      // zone-owner kernel unless one, "L" for the level-sorted order
+      char buf[64], tp[32] = "";
+      const ZoneForm f = stage_form(c, Variant{cand[i].nsub, cand[i].tpb}, (int)nblk(c));
+      if (f.threads != 256) std::snprintf(tp, sizeof tp, "t%d", f.threads);
+      if (cand[i].nsub == 1 && f.parts > 1) std::snprintf(tp, sizeof tp, "t%dp%d", f.threads, f.parts);
       std::snprintf(buf, sizeof buf, "%s\"%d%s%s\": %.4f", i ? ", " : "", cand[i].nsub, tp, cand[i].order ? "L" : "",
                     cand[i].ms);
       c->tune_log += buf;

@@ -843,14 +843,9 @@ hipError_t go_ns(int n, hipStream_t st, const StageArgs& a) {
 hipError_t launch_stage2(const Shape& s, int precision, int ncu, const StageArgs& a, hipStream_t st) {
   const int n = a.topo.h.n_blocks;
   if (s.nf == 4) {
-    // Up to two halves for each of the device's compute units are one round of workgroups, and
-    // their latency counts; beyond (256 blocks on the MI355X), thirds of blocks leave room for three (FP64) or four (mixed) on a
-    // unit.  2,944 blocks mixed: 88.9 us a stage in thirds against 94.3 in halves (100 without
-    // SHARE); 1,024 blocks FP64: 41.8 against 43.2; 256 blocks mixed: 10.5 us in halves, 10.8 to
-    // 11.4 in thirds, 11.0 against 11.3 with SHARE.
-    if (n > ncu) {
-      if (precision == 0) return go_ns<double, double, false, 11, 448>(n, st, a);
-      return go_ns<float, float, true, 11, 512>(n, st, a);
+    if (zone_form(s, precision, n, ncu).parts == 3) {
+      if (precision == 0) return go_ns<double, double, false, 11, kNsThirds>(n, st, a);
+      return go_ns<float, float, true, 11, kNsThirdsMixed>(n, st, a);
     }
     if (precision == 0) return go_ns<double, double, false, 17, kNsThreads>(n, st, a);
     return go_ns<float, float, false, 17, kNsThreads>(n, st, a);

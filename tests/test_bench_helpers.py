@@ -77,3 +77,10 @@ def test_cpu_model_names_the_host_processor():
         want = next((ln.split(":", 1)[1].strip() for ln in open("/proc/cpuinfo") if ln.startswith("model name")), None)
         if want:
             assert name.startswith(want)
+
+
+def test_traffic_key_tells_splits_of_blocks_apart():
+    """Halves and thirds of blocks are other kernels than whole ones of as many threads."""
+    form = {"stage_tiles": 1, "stage_threads": 512, "stage_parts": 3}
+    assert bench.traffic_key("c3", form, "stage") == "c3 nsub 1 t512 p3"
+    assert bench.traffic_key("c3", dict(form, stage_parts=1), "stage") == "c3 nsub 1 t512"

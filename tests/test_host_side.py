@@ -206,3 +206,44 @@ for precision in (W.FP64, W.MIXED):
         assert [g for name, g in got if "k_filter2" in name] == [want], (len(lv), got)
         s.close()
 ''')
+
+
+def test_stats_name_the_workgroups_that_run(tmp_path):
+    """stage_threads and stage_parts are those of a launch over the current grid, stage_ran those
+    of the last launch, analysis_workgroup the analysis's; every shape, precision and split."""
+    run(tmp_path, '''
+for make, level in ((W.C1, 3), (W.C2, 2), (W.C2, 3), (W.DSL, 3), (W.DSL, 4), (W.DSL, 5), (W.C4, 2)):
+    for precision in (W.FP64, W.MIXED):
+        cfg = make(jmax=6, form=W.FORM_FUSED, precision=precision).replace(max_blocks=6000)
+        lv, co = W.uniform_forest(cfg, level)
+        s = pool_free_solver(cfg, lv, co)
+        for nsub, reps in ((0, 0), (2, 0), (0, 1)):
+            s.tune(nsub=nsub, reps=reps)
+            if reps:
+                keys = s.stats()["tune_ms"]
+                ran = {(g, t) for name, g, t in launches() if "k_stage" in name}
+                for k in keys:
+                    if k.startswith("1t") and not k.endswith("L"):
+                        t, p = (k[2:].split("p") + ["1"])[:2]
+                        assert ((len(lv) * int(p) + 7) // 8 * 8, int(t)) in ran, (k, ran)
+            launches()
+            s.set_sweep(0)
+            s.rk4(0.0, cfg.dt)
+            s.mr_pass()
+            st = s.stats()
+            got = launches()
+            stage = {(g, t) for name, g, t in got if "k_stage" in name}
+            (wg, t), = stage
+            assert st["stage_threads"] == t and st["stage_ran"] == [st["stage_parts"], t], (cfg.name, st, got)
+            items = (len(lv) * st["stage_parts"] + 7) // 8 * 8
+            assert wg == (min(items, st["grid"]) if t == 256 else items)   # (256: a loop over items)
+            (t,) = {t for name, g, t in got if "k_mr" in name}
+            assert st["analysis_workgroup"] == t, (cfg.name, st, got)
+            # a larger grid: the last launch keeps its name
+            s.refine_all()
+            assert s.stats()["stage_ran"] == st["stage_ran"]
+            s.init_forest(lv, co)
+            s._chk(M.lib().mrb_load_blocks(s.h, 8, 1))
+            launches()
+        s.close()
+''')
