@@ -182,25 +182,32 @@ mrb_status mrb_stats(mrb_ctx *ctx, char *json, int cap);
  * events on the solver's stream and mrb_stats reports the accumulated device
  * time and algorithmic bytes per kernel kind; enable = 0 stops and clears. */
 mrb_status mrb_timing(mrb_ctx *ctx, int enable);
-/* Block tilings (the autotuner).  nsub > 0 forces nsub sub-tiles per axis (one
- * workgroup each) for the fused stage sweep, and for the overlapped-tile RK4 step
- * (mrb_set_sweep mode 3) where that tiling is compiled; nsub = 0 with reps > 0 times reps dry
+/* Block tilings (the autotuner).  nsub > 0 forces nsub sub-tiles per axis for the fused
+ * stage sweep (nsub = 1: whole blocks, by the kernel that resolves owners per zone; it
+ * takes a workgroup per block, for Navier-Stokes one per half or third of a block), and for
+ * the overlapped-tile RK4 step (mrb_set_sweep mode 3) where that tiling is compiled.
+ * nsub = 1 is accepted for every shape.  nsub = 0 with reps > 0 times reps dry
  * sweeps (four stages into k1..k3/u_new, the state u is not advanced) of every
  * compiled stage tiling, in forest (Morton) order and in level-sorted order, on the
  * current forest and keeps the fastest pair, then does the
- * same for the analysis kernel (one pass; flags are recomputed) and, if the last
- * refinement plan is still the uploaded one (right after mrb_refine_all), for the
- * refinement kernel (re-run on the same parents), and the analysis of whole blocks with
- * larger workgroups where compiled; on the chosen stage tiling it also
+ * same for the analysis kernel (one pass; flags are recomputed) and for the analysis of
+ * whole blocks with larger workgroups where compiled, and, if the last refinement plan is
+ * still the uploaded one (right after mrb_refine_all), times the refinement kernel, which
+ * has one form, for the log; on the chosen stage tiling it also
  * times the whole sweep as four launches against one launch with grid barriers, and,
  * if every leaf is on one level and the shape has the kernel, every tiling of the
  * overlapped-tile RK4 step against the stage launches (see mrb_set_sweep).  Every
  * candidate is timed over five rounds and its fastest round
  * counts.  nsub > 0 with reps < 0 also sets -reps threads per workgroup for the stage
- * sweep, for the analysis of whole blocks and for the tile step's folded forms (first
- * analysis, refinement, second analysis, then also on nsub sub-tiles), each where that
- * form is compiled; MRB_E_ARG if none is.  nsub = 0 with reps = 0 returns to the built-in choices.  *chosen (may
- * be NULL) receives the stage tiling in use.
+ * sweep (whole blocks: the kernels that resolve owners per point, or the zone kernel by
+ * its own number), for the analysis of whole blocks and for the tile step's folded forms
+ * (first analysis, refinement, second analysis, then also on nsub sub-tiles), each where
+ * that form is compiled; MRB_E_ARG if none is.  nsub = 0 with reps = 0 returns to the
+ * built-in choices.  *chosen (may be NULL) receives the stage tiling in use.
+ * mrb_stats: stage_tiles, stage_threads and stage_parts are the sub-tiles per axis, the
+ * threads and the workgroups per block of a stage launch over the current grid, stage_ran
+ * [workgroups per block, threads] of the last one; analysis_threads is the size chosen for
+ * the analysis and analysis_workgroup the one it runs with.
  * Not a step of the method: a schedule choice. */
 mrb_status mrb_tune(mrb_ctx *ctx, int nsub, int reps, double dt, int *chosen);
 /* Graph replay in mrb_step: the refinement, the four RK stages and the first analysis

@@ -278,7 +278,8 @@ class Solver:
         return fl, md
 
     def tune(self, nsub: int = 0, reps: int = 0) -> int:
-        """Force (nsub > 0), autotune (reps > 0) or reset the stage tiling; returns the tiling in use."""
+        """Force (nsub > 0; 1: whole blocks, for every shape), autotune (reps > 0) or reset the stage
+        tiling; returns the tiling in use."""
         ch = ctypes.c_int()
         self._chk(lib().mrb_tune(self.h, nsub, reps, self.cfg.dt, ctypes.byref(ch)))
         return ch.value

@@ -2977,11 +2977,12 @@ mrb_status mrb_tune(mrb_ctx* c, int nsub, int reps, double dt, int* chosen) {
   int v[8];
   const int nv = stage_variants(c->shape, c->cfg.precision, v, 8);
   if (nsub > 0) {
-    bool ok = false;
+    // (whole blocks: every shape has the zone-owner kernel)
+    bool ok = nsub == 1;
     for (int i = 0; i < nv; ++i) ok = ok || v[i] == nsub;
     if (!ok) return fail(c, MRB_E_ARG, "tune: tiling not compiled for this shape and precision");
     c->nsub = nsub;
-    c->tpb = 256;
+    c->tpb = nsub == 1 ? zone_threads(c->shape) : 256;
     int tv[8];
     const int nt = rk4t_variants(c->shape, c->cfg.precision, tv, 8);
     for (int i = 0; i < nt; ++i)

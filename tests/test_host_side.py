@@ -247,3 +247,45 @@ for make, level in ((W.C1, 3), (W.C2, 2), (W.C2, 3), (W.DSL, 3), (W.DSL, 4), (W.
             launches()
         s.close()
 ''')
+
+
+def test_whole_blocks_can_be_forced_for_every_shape(tmp_path):
+    """tune(nsub=1) is accepted for every shape and precision and takes the kernel that the
+    default and the autotuner mean by one sub-tile; workgroup sizes are named by reps < 0 as
+    before, and what is not compiled is refused as before."""
+    run(tmp_path, '''
+for make, level, zone, points in ((W.C1, 3, "k_stage2", 256), (W.C2, 3, "k_stage2", 512), (W.DSL, 3, "k_stage_ns", 1024),
+                                  (W.C4, 2, "k_stage3", 512)):
+    for precision in (W.FP64, W.MIXED):
+        cfg = make(jmax=6, form=W.FORM_FUSED, precision=precision).replace(max_blocks=6000)
+        s = pool_free_solver(cfg, *W.uniform_forest(cfg, level))
+        s.set_sweep(0)
+
+        def stage():
+            launches()
+            s.rk4(0.0, cfg.dt)
+            return " ".join(sorted({name for name, g, t in launches() if "k_stage" in name}))
+
+        default = stage()
+        assert zone in default
+        for reps in (0, -{"k_stage2": 448 if cfg.bs == 17 else 384, "k_stage_ns": 576, "k_stage3": 448}[zone]):
+            s.tune(nsub=2)
+            assert "7k_stage" in stage()
+            assert s.tune(nsub=1, reps=reps) == 1
+            assert stage() == default, (cfg.name, precision)
+            assert s.stats()["stage_tiles"] == 1
+        chosen = s.tune(reps=1)
+        assert s.tune(nsub=chosen) == chosen
+        try:                                   # the point-owner kernel, where it is compiled
+            s.tune(nsub=1, reps=-points)
+            assert (zone if (cfg.name, precision) == ("DSL", W.FP64) else "7k_stage") in stage()
+        except M.MrbError as e:
+            assert e.code == -1 and (cfg.name, precision) == ("C4", W.FP64)
+        for bad in ((3, 0), (1, -768), (8, 0)):
+            try:
+                s.tune(nsub=bad[0], reps=bad[1])
+                assert False, bad
+            except M.MrbError as e:
+                assert e.code == -1
+        s.close()
+''')

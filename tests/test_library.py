@@ -1329,3 +1329,44 @@ def test_ns_stage_on_both_sides_of_two_workgroups_a_unit(seed, n, which):
         out.append(s.read_blocks())
         s.close()
     assert np.array_equal(_bits(out[0]), _bits(out[1]))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("which", ["C4 FP64", "DSL FP64", "C3 mixed"])
+def test_the_autotuners_choice_can_be_forced(which):
+    """The tiling that the autotuner returns is accepted by tune(nsub) in another solver, and one
+    sub-tile runs the default kernel: FP64 bitwise the oracle, mixed bitwise the sub-tiles."""
+    name, precision = which.split()
+    make, dim, zone = {"C4": (W.C4, 3, 448), "DSL": (W.DSL, 2, 576), "C3": (W.C3, 2, 576)}[name]
+    cfg = make(jmax=4, form=W.FORM_FUSED, max_blocks=3000)
+    lv, co = W.random_graded_forest(dim, 3, 1, 0.4, 2)
+    o = oracle.Oracle(cfg)
+    o.init_forest(lv, co)
+    lv, co = o.read_forest()
+    data = W.sample(cfg, lv, co)
+    if precision == "mixed":
+        cfg = cfg.replace(precision=W.MIXED)
+    s = M.Solver(cfg)
+    s.init_forest(lv, co)
+    s.load_blocks(data)
+    chosen = s.tune(reps=1)
+    s.close()
+    out = []
+    for nsub in (chosen, 1, 2):
+        s = M.Solver(cfg)
+        assert s.tune(nsub=nsub) == nsub
+        s.init_forest(lv, co)
+        s.load_blocks(data)
+        if nsub == 1:
+            assert s.stats()["stage_threads"] == zone
+        for k in range(2):
+            s.rk4(k * cfg.dt, cfg.dt)
+        out.append(s.read_blocks())
+        s.close()
+    if precision == "FP64":
+        o.load_blocks(data)
+        for k in range(2):
+            o.rk4(k * cfg.dt, cfg.dt)
+        out.append(o.read_blocks())
+    for a in out[1:]:
+        assert np.array_equal(_bits(a), _bits(out[0]))
