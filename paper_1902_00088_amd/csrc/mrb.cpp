@@ -914,11 +914,14 @@ int pick_tpb(const mrb_ctx* c, int nsub) { return c->nsub == nsub ? c->tpb : 256
 // (FP64), 68 against 107 (mixed), 8 blocks 42 against 44; 1,024 blocks of 33^2 53 against 73,
 // 64 blocks 22 against 24; 1,024 Navier-Stokes blocks 158 against 267; 1,024 blocks of 17^2
 // 28 against 28, 4 to 256 blocks 16-20 against 19-23.  Only where 4 x 4 sub-tiles of 33^2
-// blocks still leave compute units idle do those win: 16 blocks 20.7 against 22.0 us,
-// Navier-Stokes 28.1 against 31.2.
+// blocks still leave compute units idle do those win: below two workgroups a unit in
+// advection (19 to 31 blocks on two levels 26.5-27.6 us against 28.3-29.4 FP64, 27.0-27.6
+// against 26.7-28.4 mixed; 34 blocks 29.0 against 29.1 and 29.0 against 28.0), up to one in
+// Navier-Stokes (16 blocks 28.4 against 31.2 us, 19 blocks 41.2 against 37.6).
 Variant pick_stage(const mrb_ctx* c) {
   const Variant zoned{1, zone_threads(c->shape)};
-  const bool tiny = c->shape.dim == 2 && c->shape.bs == 33 && 16 * (long)nblk(c) <= c->ncu;
+  const long tiles = 16 * (long)nblk(c);
+  const bool tiny = c->shape.dim == 2 && c->shape.bs == 33 && (c->shape.nf == 1 ? tiles < 2L * c->ncu : tiles <= c->ncu);
   if ((c->nsub == 0 && !tiny) || (c->nsub == 1 && c->tpb == zoned.tpb)) return zoned;
   const int nsub = pick_nsub(c);
   return Variant{nsub, pick_tpb(c, nsub)};

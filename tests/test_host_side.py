@@ -289,3 +289,33 @@ for make, level, zone, points in ((W.C1, 3, "k_stage2", 256), (W.C2, 3, "k_stage
                 assert e.code == -1
         s.close()
 ''')
+
+
+@pytest.mark.parametrize("units", [64, 256])
+def test_default_stage_of_few_blocks(tmp_path, units):
+    """Blocks of 33^2 take 4 x 4 sub-tiles while these are fewer than two workgroups a compute
+    unit (advection) or at most one (Navier-Stokes), whole blocks beyond."""
+    run(tmp_path, f'''
+units = {units}
+host.host_compute_units(units)
+for make, last in ((W.C2, units // 8 - 1), (W.DSL, units // 16)):
+    for precision in (W.FP64, W.MIXED):
+        cfg = make(jmax=4, form=W.FORM_FUSED, precision=precision).replace(max_blocks=500)
+        seen = set()
+        for refined in range(13):
+            for level in (1, 2):
+                lv, co = W.uniform_forest(cfg, level)
+                if refined > len(lv):
+                    continue
+                kids = np.concatenate([2 * co[:refined] + np.array([i, j]) for i in (0, 1) for j in (0, 1)])
+                lv = np.r_[lv[refined:], np.full(len(kids), level + 1, np.int8)]
+                co = np.r_[co[refined:], kids.astype(np.int32)]
+                s = pool_free_solver(cfg, lv, co)
+                s.rk4(0.0, cfg.dt)
+                tiled = any("7k_stage" in name for name, g, t in launches())
+                assert tiled == (len(lv) <= last), (cfg.name, len(lv), last)
+                assert s.stats()["stage_tiles"] == (4 if tiled else 1)
+                seen.add(tiled)
+                s.close()
+        assert seen == {{True, False}}
+''')
