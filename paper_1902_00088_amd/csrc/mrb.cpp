@@ -918,8 +918,15 @@ int pick_tpb(const mrb_ctx* c, int nsub) { return c->nsub == nsub ? c->tpb : 256
 // advection (19 to 31 blocks on two levels 26.5-27.6 us against 28.3-29.4 FP64, 27.0-27.6
 // against 26.7-28.4 mixed; 34 blocks 29.0 against 29.1 and 29.0 against 28.0), up to one in
 // Navier-Stokes (16 blocks 28.4 against 31.2 us, 19 blocks 41.2 against 37.6).
+// And from 49,152 blocks of 17^2 on, where a stage streams its arrays (114 MB each in FP64)
+// from memory, whole blocks with 256 threads and the owners per point: 49,153 blocks 915 us
+// against 926 (FP64), 812 against 804 (mixed); 65,536 blocks 1,166 against 1,236 and 1,076
+// against 1,141; 262,144 blocks 4,572 against 4,878 and 4,348 against 4,655; but 34,816 blocks
+// 640 against 603 and 557 against 531.
+constexpr long kStreamed17 = 49152;
 Variant pick_stage(const mrb_ctx* c) {
   const Variant zoned{1, zone_threads(c->shape)};
+  if (c->nsub == 0 && c->shape.dim == 2 && c->shape.bs == 17 && (long)nblk(c) >= kStreamed17) return Variant{1, 256};
   const long tiles = 16 * (long)nblk(c);
   const bool tiny = c->shape.dim == 2 && c->shape.bs == 33 && (c->shape.nf == 1 ? tiles < 2L * c->ncu : tiles <= c->ncu);
   if ((c->nsub == 0 && !tiny) || (c->nsub == 1 && c->tpb == zoned.tpb)) return zoned;

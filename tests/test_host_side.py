@@ -319,3 +319,32 @@ for make, last in ((W.C2, units // 8 - 1), (W.DSL, units // 16)):
                 s.close()
         assert seen == {{True, False}}
 ''')
+
+
+def test_default_stage_of_many_small_blocks(tmp_path):
+    """Forests of 49,152 blocks of 17^2 and more take the point-owner kernel on whole blocks,
+    smaller ones and other shapes of as many blocks the zone-owner kernel; forcing whole blocks
+    still means the latter."""
+    run(tmp_path, '''
+def refined(cfg, level, k):
+    lv, co = W.uniform_forest(cfg, level)
+    order = morton(co)
+    lv, co = lv[order], co[order]
+    kids = np.concatenate([2 * co[:k] + np.array([i, j]) for i in (0, 1) for j in (0, 1)])
+    return np.r_[lv[k:], np.full(len(kids), level + 1, np.int8)], np.r_[co[k:], kids.astype(np.int32)]
+
+
+for precision in (W.FP64, W.MIXED):
+    for make, k, want in ((W.C1, 10922, "k_stage2"), (W.C1, 10923, "7k_stage"), (W.C2, 10923, "k_stage2")):
+        cfg = make(jmax=8, form=W.FORM_FUSED, precision=precision).replace(max_blocks=50000)
+        lv, co = refined(cfg, 7, k)
+        s = pool_free_solver(cfg, lv, co)
+        s.rk4(0.0, cfg.dt)
+        got = [(name, t) for name, g, t in launches() if "k_stage" in name]
+        assert len(got) == 4 and all(want in name for name, t in got), (cfg.name, len(lv), got)
+        assert s.stats()["stage_threads"] == got[0][1] and s.stats()["stage_tiles"] == 1
+        s.tune(nsub=1)
+        s.rk4(0.0, cfg.dt)
+        assert all("k_stage2" in name for name, g, t in launches())
+        s.close()
+''')

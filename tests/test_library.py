@@ -1370,3 +1370,62 @@ def test_the_autotuners_choice_can_be_forced(which):
         out.append(o.read_blocks())
     for a in out[1:]:
         assert np.array_equal(_bits(a), _bits(out[0]))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("which,tpb", [("C1", 256), ("C2", 256), ("C2", 512), ("C4", 256), ("C4", 512)])
+def test_point_owner_stage_of_whole_blocks(which, tpb):
+    """The point-owner stage kernel on whole blocks, named by its workgroup size, on random
+    graded forests: FP64 bitwise the oracle (where it is compiled), mixed bitwise the default."""
+    make, dim = {"C1": (W.C1, 2), "C2": (W.C2, 2), "C4": (W.C4, 3)}[which]
+    cfg = make(jmax=5 if dim == 2 else 4, form=W.FORM_FUSED, max_blocks=3000)
+    lv, co = W.random_graded_forest(dim, 4 if dim == 2 else 3, 2, 0.3)
+    o = oracle.Oracle(cfg)
+    o.init_forest(lv, co)
+    lv, co = o.read_forest()
+    data = W.sample(cfg, lv, co)
+    o.load_blocks(data)
+    for k in range(2):
+        o.rk4(k * cfg.dt, cfg.dt)
+
+    def run(precision, reps):
+        s = M.Solver(cfg.replace(precision=precision))
+        s.init_forest(lv, co)
+        s.load_blocks(data)
+        if reps:
+            s.tune(nsub=1, reps=reps)
+            assert s.stats()["stage_threads"] == tpb
+        for k in range(2):
+            s.rk4(k * cfg.dt, cfg.dt)
+        out = s.read_blocks()
+        s.close()
+        return out
+
+    if dim == 2:
+        assert np.array_equal(_bits(run(W.FP64, -tpb)), _bits(o.read_blocks()))
+    assert np.array_equal(_bits(run(W.MIXED, -tpb)), _bits(run(W.MIXED, 0)))
+
+
+@pytest.mark.gpu
+def test_stage_rule_of_many_small_blocks_keeps_values():
+    """49,153 blocks of 17^2 on two levels, the first count past the rule's line: the default
+    stage equals the zone-owner kernel bit for bit in both precisions."""
+    cfg = W.C1(jmax=8, form=W.FORM_FUSED).replace(max_blocks=49200)
+    lv, co = W.uniform_forest(cfg, 7)
+    fine = np.arange(len(lv)) < 10923
+    kids = np.concatenate([2 * co[fine] + np.array([i, j]) for i in (0, 1) for j in (0, 1)])
+    lv, co = np.r_[lv[~fine], np.full(len(kids), 8, np.int8)], np.r_[co[~fine], kids.astype(np.int32)]
+    for precision in (W.FP64, W.MIXED):
+        out = []
+        for nsub in (0, 1):
+            s = M.Solver(cfg.replace(precision=precision))
+            s.init_forest(lv, co)
+            assert s.num_blocks() == 49153
+            s.load_blocks(W.sample(cfg, *s.read_forest()))
+            if nsub:
+                s.tune(nsub=nsub)
+            assert s.stats()["stage_threads"] == (448 if nsub else 256)
+            s.rk4(0.0, cfg.dt)
+            out.append(s.read_blocks())
+            s.close()
+        assert np.array_equal(_bits(out[0]), _bits(out[1]))
