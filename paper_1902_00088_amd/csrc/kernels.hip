@@ -1628,24 +1628,36 @@ __global__ void __launch_bounds__(256) k_read(ReadArgs A) {
   }
 }
 
-// whole-block copy from a contiguous [n][bsz] array into the blocks' pool slots, 1,024 values a
-// workgroup, all loads in flight.  The slots come from the block descriptors: a list of them
-// copied to the device first cost a small grid more than the copy itself (a load of 40 blocks
-// of 17^2 took 28 us, now 19; 1,793 of 17^3, 141 MB: the kernel 25 to 27 us either way).
+// whole-block copy from a contiguous [n][BSZ] array into the blocks' pool slots, 1,024 values a
+// workgroup whatever the blocks' size, all loads in flight.  The slots come from the block
+// descriptors: a list of them copied to the device first cost a small grid more than the copy
+// itself (a load of 40 blocks of 17^2 took 28 us, now 19).  Memory bound: 65,536 blocks of 33^2
+// take 203 us (5.6 TB/s) and 262,144 of 17^2 219 us (5.5 TB/s), against 261 and 322 us with the
+// blocks themselves cut into parts of 1,024 values, most of the last one empty.
 constexpr int kScatter = 1024;
+template <int BSZ>
 __global__ void __launch_bounds__(256) k_scatter(ScatterArgs A) {
-  const int parts = (A.bsz + kScatter - 1) / kScatter;
-  const XcdWork it(A.topo.h.n_blocks * parts);   // one work item per workgroup
+  const int total = A.topo.h.n_blocks * BSZ;   // (below 2^31, as the pool)
+  const XcdWork it((total - 1) / kScatter + 1);   // one work item per workgroup
   if (!it.ok()) return;
-  const int b = it.w / parts, q0 = (it.w - b * parts) * kScatter + threadIdx.x;
-  const double* src = A.src + (size_t)b * A.bsz;
-  double* dst = A.u + (size_t)A.topo.blk()[b].slot * A.bsz;
+  // the blocks the workgroup's values belong to: at most NB, their slots loaded once each
+  constexpr int NB = (kScatter + BSZ - 2) / BSZ + 1;
+  const BlockDesc* blk = A.topo.blk();
+  const int first = it.w * kScatter, b0 = first / BSZ, r0 = first - b0 * BSZ;
+  int to[NB];   // pool position of a block's value 0, less its place in the array
+#pragma unroll
+  for (int k = 0; k < NB; ++k) to[k] = (blk[min(b0 + k, A.topo.h.n_blocks - 1)].slot - b0 - k) * BSZ;
   double v[kScatter / 256];
 #pragma unroll
-  for (int i = 0; i < kScatter / 256; ++i) v[i] = src[min(q0 + 256 * i, A.bsz - 1)];
+  for (int i = 0; i < kScatter / 256; ++i) v[i] = A.src[min((int)threadIdx.x + 256 * i, total - 1 - first) + first];
 #pragma unroll
-  for (int i = 0; i < kScatter / 256; ++i)
-    if (q0 + 256 * i < A.bsz) dst[q0 + 256 * i] = v[i];
+  for (int i = 0; i < kScatter / 256; ++i) {
+    const int q = threadIdx.x + 256 * i;
+    int t = to[0];
+#pragma unroll
+    for (int k = 1; k < NB; ++k) t = r0 + q >= k * BSZ ? to[k] : t;
+    if (q <= total - 1 - first) A.u[t + first + q] = v[i];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2034,7 +2046,13 @@ hipError_t launch_zero(void* p, size_t bytes, hipStream_t st) {
 }
 
 hipError_t launch_scatter(const ScatterArgs& a, hipStream_t st) {
-  return go(k_scatter, a.topo.h.n_blocks * ((a.bsz + kScatter - 1) / kScatter), 0, st, a);
+  if (a.topo.h.n_blocks == 0) return hipSuccess;
+  const int grid = (a.topo.h.n_blocks * a.bsz - 1) / kScatter + 1;
+  if (a.bsz == 17 * 17) return go(k_scatter<17 * 17>, grid, 0, st, a);
+  if (a.bsz == 33 * 33) return go(k_scatter<33 * 33>, grid, 0, st, a);
+  if (a.bsz == 4 * 33 * 33) return go(k_scatter<4 * 33 * 33>, grid, 0, st, a);
+  if (a.bsz == 17 * 17 * 17) return go(k_scatter<17 * 17 * 17>, grid, 0, st, a);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace mrb

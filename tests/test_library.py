@@ -1429,3 +1429,27 @@ def test_stage_rule_of_many_small_blocks_keeps_values():
             out.append(s.read_blocks())
             s.close()
         assert np.array_equal(_bits(out[0]), _bits(out[1]))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("on_device", [False, True])
+@pytest.mark.parametrize("which", ["C1", "C2", "C3", "C4"])
+def test_loaded_blocks_reach_their_slots(which, on_device):
+    """Blocks loaded into a forest whose slots are out of order (refined in part, coarsened
+    back in part) read back bit for bit: workgroups that hold several blocks, parts of two, and
+    a last one that is cut off, for each size of a block."""
+    import torch
+    make = {"C1": W.C1, "C2": W.C2, "C3": W.C3, "C4": W.C4}[which]
+    cfg = make(jmax=4 if which != "C4" else 3, form=W.FORM_FUSED, max_blocks=900)
+    s = M.Solver(cfg)
+    s.init_forest(*W.uniform_forest(cfg, 2))
+    s.load_blocks(W.sample(cfg, *s.read_forest()))
+    rng = np.random.default_rng(3)
+    for k in range(3):
+        s.refine_marked((rng.random(s.num_blocks()) < 0.2) & (s.read_forest()[0] < cfg.jmax))
+        s.coarsen(np.where(rng.random(s.num_blocks()) < 0.9, -1, 0))
+        lv, co = s.read_forest()
+        data = W.sample(cfg, lv, co) + k
+        s.load_blocks(torch.as_tensor(data, device="cuda") if on_device else data)
+        assert np.array_equal(_bits(s.read_blocks()), _bits(data)), (k, len(lv))
+    s.close()
