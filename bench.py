@@ -39,7 +39,7 @@ def counter_traffic(key):
     try:
         text = open(path).read()
         src = open(os.path.join(csrc, "kernels.hip"), "rb").read()
-        for name in ("column3.hip", "plane2.hip", "device.hpp"):   # the kernels' other sources
+        for name in ("column3.hip", "plane2.hip", "device.hpp", "internal.hpp"):   # the kernels' other sources
             if os.path.exists(os.path.join(csrc, name)):
                 src += open(os.path.join(csrc, name), "rb").read()
         sha = hashlib.sha256(src).hexdigest()

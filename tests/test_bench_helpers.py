@@ -84,3 +84,20 @@ def test_traffic_key_tells_splits_of_blocks_apart():
     form = {"stage_tiles": 1, "stage_threads": 512, "stage_parts": 3}
     assert bench.traffic_key("c3", form, "stage") == "c3 nsub 1 t512 p3"
     assert bench.traffic_key("c3", dict(form, stage_parts=1), "stage") == "c3 nsub 1 t512"
+
+
+def test_counter_traffic_is_void_once_any_kernel_source_changes(tmp_path, monkeypatch):
+    """Workgroup sizes and argument layouts stand in headers: the summary's hash covers them."""
+    src = b"// kernel source\n"
+    names = ("column3.hip", "plane2.hip", "device.hpp", "internal.hpp")
+    sha = hashlib.sha256(src + b"".join(n.encode() for n in names)).hexdigest()
+    _fake_tree(tmp_path, src, sha, ["traffic_bytes_per_launch c2 nsub 4: 2047807"])
+    csrc = tmp_path / "paper_1902_00088_amd" / "csrc"
+    for n in names:
+        (csrc / n).write_bytes(n.encode())
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    assert bench.counter_traffic("c2 nsub 4") == 2047807.0
+    for n in names:
+        (csrc / n).write_bytes(b"changed")
+        assert bench.counter_traffic("c2 nsub 4") is None, n
+        (csrc / n).write_bytes(n.encode())
