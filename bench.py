@@ -12,7 +12,8 @@ mixed fused (FP32 stencil and slopes, FP64 state).  The headline value is the
 mixed fused form.  Per-kernel device times come from HIP events on the solver's
 stream in a second, instrumented pass over the same steps.
 
-Prints one JSON line.
+Prints one JSON line: the headline figures and a summary of the other workloads.  `--detail FILE`
+also writes the whole record (per-kernel times, tuning logs, host times, the predictor study).
 """
 import argparse
 import json
@@ -315,8 +316,50 @@ def headline(args, res, acc=None):
     }
 
 
+def _short(v):
+    """v with its floats to six significant digits."""
+    if isinstance(v, float):
+        return float(f"{v:.6g}")
+    if isinstance(v, dict):
+        return {k: _short(x) for k, x in v.items()}
+    if isinstance(v, (list, tuple)):
+        return [_short(x) for x in v]
+    return v
+
+
+def _pick(d, *keys):
+    return None if d is None else {k: d[k] for k in keys if k in d}
+
+
+def summary(out):
+    """The printed line's record: every headline field of `out` with the value as measured, and
+    of each form, workload and study what its result comes to (a reader of the line may hold
+    only so much of it; the whole record has tens of kilobytes)."""
+    form = lambda f: {k: _pick(v, "value", "ms_per_step", "blocks_final", "sweep_launch") for k, v in f.items()}
+    acc = lambda a: _pick(a, "steps", "max_rel_inf", "within_1e-5")
+    line = {}
+    for k, v in out.items():
+        if k == "forms":
+            v = form(v)
+        elif k == "mixed_accuracy":
+            v = acc(v)
+        elif k in ("c3", "c4"):
+            v = dict(v, forms=form(v["forms"]), mixed_accuracy=acc(v["mixed_accuracy"]))
+            for q in list(v):
+                if q.startswith("speedup_"):
+                    v[q] = _pick(v[q], "speedup")
+                elif q.startswith("roofline"):
+                    v[q] = _pick(v[q], "achieved", "peak", "unit", "frac", "traffic", "avg_launch_us")
+        elif k == "predictor":
+            v = {name: _pick(c, "test_accuracy", "block_updates_saved", "within_bound", "degenerate")
+                 for name, c in v.items()}
+        line[k] = v if k in ("value", "ms_per_step") else _short(v)
+    return line
+
+
 def main():
     ap = argparse.ArgumentParser()
+    ap.add_argument("--detail", default="", help="also write the whole record to this file")
     ap.add_argument("--gpus", type=int, default=1)
     ap.add_argument("--steps", type=int, default=500)
     ap.add_argument("--warmup", type=int, default=24)
@@ -440,7 +483,10 @@ def main():
     if not args.no_cpu:
         print("bench: cpu baseline (oracle)", file=sys.stderr, flush=True)
         out["cpu_baseline"] = cpu_baseline(W, base, args.cpu_seconds)
-    print(json.dumps(out), flush=True)
+    if args.detail:
+        with open(args.detail, "w") as f:
+            json.dump(out, f)
+    print(json.dumps(summary(out)), flush=True)
 
 
 if __name__ == "__main__":

@@ -101,3 +101,43 @@ def test_counter_traffic_is_void_once_any_kernel_source_changes(tmp_path, monkey
         (csrc / n).write_bytes(b"changed")
         assert bench.counter_traffic("c2 nsub 4") is None, n
         (csrc / n).write_bytes(n.encode())
+
+
+def test_printed_line_is_short_and_keeps_the_headline():
+    """The line holds every headline field as measured and a summary of the rest, in less than
+    the 4 KiB that a reader of a run's tail surely has; the whole record takes many times that."""
+    import argparse
+    import json
+    kernels = {k: {"launches": 80, "ms": 0.8416951234567, "bytes": 1605795840.0}
+               for k in ("stage", "ghost", "rhs_plain", "rk4_tile", "mr", "refine", "coarsen", "topology", "read")}
+    form = {"value": 3543684.2133620796, "ms_per_step": 0.01806030000039982, "block_updates": 1280, "blocks_initial": 16,
+            "blocks_final": 16, "sweep_block_updates_per_s": 5.04e6, "kernels": kernels, "stage_tiles": 1,
+            "stage_threads": 384, "stage_parts": 1, "sweep_launch": "rk4_tile",
+            "host_us_per_step": {f"phase{i}": 0.1234567890123 for i in range(12)},
+            "tune_ms": {f"key{i}": 0.1234567890123 for i in range(60)}, "rk4_tile": {"tiles": 1}}
+    forms = {n: dict(form) for n in ("fp64_plain", "fp64_fused", "mixed_fused")}
+    acc = {"steps": 20, "topology": "FP64 run's flags replayed", "same_forest": True, "max_rel_inf": 3.04376123456789e-08,
+           "rel_inf_per_field": {"phi": 1e-9}, "rel_l2_per_field": {"phi": 1e-9}, "within_1e-5": True}
+    args = argparse.Namespace(steps=20, warmup=5)
+    out = bench.headline(args, forms, acc)
+    for w in ("c4", "c3"):
+        out[w] = {"workload": "w" * 140, "forms": forms, "mixed_accuracy": acc,
+                  "speedup_mixed_fused_vs_fp64_plain": bench.speedup_entry(forms, acc),
+                  "speedup_mixed_fused_vs_fp64_fused": bench.speedup_entry(forms, acc, base="fp64_fused"),
+                  "roofline_stage_mixed": dict(out["roofline"])}
+    study = {"test_accuracy": 0.5794371234, "block_updates_saved": 0.20192645825631406, "within_bound": False,
+             "degenerate": False, "guards": {"0.0": {f"k{i}": 0.123456789 for i in range(40)}}}
+    out["predictor"] = {"C5_mixing_layer": study, "swirl_moving_fronts": study}
+    out["cpu_baseline"] = {"value": 13383.8, "unit": "block-updates/s", "cores": 16, "kind": "oracle", "sample": "s" * 110,
+                           "cpu_model": "m" * 60, "host_threads_available": 16,
+                           "single_thread": {"value": 1116.98, "cores": 1, "sample": "s" * 90}}
+    line = json.dumps(bench.summary(out))
+    assert len(line) < 4096 < len(json.dumps(out)) / 3
+    got = json.loads(line)
+    for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+              "vs_baseline", "dtype", "data", "config"):
+        assert got[k] == out[k], k
+    assert set(got) == set(out) and got["roofline"]["kernel"] == out["roofline"]["kernel"]
+    assert got["c3"]["forms"]["mixed_fused"]["ms_per_step"] == 0.0180603
+    assert got["predictor"]["C5_mixing_layer"]["block_updates_saved"] == 0.201926
+    assert bench.summary({}) == {} and bench.summary({"mixed_accuracy": None}) == {"mixed_accuracy": None}
