@@ -216,8 +216,13 @@ struct Variant {
   int tpb = 256;          // threads per workgroup (stage kernel)
 };
 
-// Launchers (kernels.hip).  grid = number of workgroups (grid-stride loops inside).
-hipError_t launch_stage(const Shape& s, int precision, Variant v, int grid, int ncu, const StageArgs& a, hipStream_t st);
+// Launchers (kernels.hip).  The stage and the analysis take at most max_grid workgroups on
+// sub-tiles and point-owner blocks, whose kernels loop over their items.  The zone-owner
+// kernels (whole blocks: column3.hip, plane2.hip), the tile step, the refinement and the copy
+// of loaded blocks have no loop: they launch a workgroup per item, and fewer would leave work
+// undone.  ncu: the device's compute units.
+hipError_t launch_stage(const Shape& s, int precision, Variant v, int max_grid, int ncu, const StageArgs& a,
+                        hipStream_t st);
 // Whole-sweep kernel, cooperative launch of at most one workgroup per compute unit
 // (and at most `max_grid`); *grid_out gets the count.  hipErrorInvalidValue if the
 // variant is not compiled.
@@ -234,7 +239,6 @@ hipError_t launch_refine2(const Shape& s, const RefineArgs& a, hipStream_t st);
 // 2D stages of whole blocks (halves or thirds of them for Navier-Stokes) and the filter
 // (plane2.hip): the stage variant of zone_threads threads (kNsThreads: of the halves)
 constexpr int kNsThreads = 576;
-// ncu: the device's compute units
 hipError_t launch_stage2(const Shape& s, int precision, int ncu, const StageArgs& a, hipStream_t st);
 hipError_t launch_filter(int ncu, const FilterArgs& a, hipStream_t st);   // NS shape only
 // threads by which a tuning names the zone-owner stage kernel of a shape (column3.hip, plane2.hip)
@@ -267,7 +271,7 @@ hipError_t launch_plain(const Shape& s, int grid, const StageArgs& a, hipStream_
 hipError_t launch_rk4t(const Shape& s, int precision, int nsub, bool analysis, bool refine, bool mothers, int tpb,
                        const Rk4tArgs& a, hipStream_t st);
 int rk4t_variants(const Shape& s, int precision, int* nsub, int cap);
-hipError_t launch_mr(const Shape& s, int nsub, int tpb, int grid, const MrArgs& a, hipStream_t st);
+hipError_t launch_mr(const Shape& s, int nsub, int tpb, int max_grid, const MrArgs& a, hipStream_t st);
 int mr_threads(const Shape& s, int nsub, int* tpb, int cap);   // workgroup sizes to ask for (256, the default, first)
 hipError_t launch_refine(const Shape& s, const RefineArgs& a, hipStream_t st);
 hipError_t launch_coarsen(const Shape& s, int grid, const CoarsenArgs& a, hipStream_t st);

@@ -495,12 +495,12 @@ __device__ __forceinline__ void subregion(int sub, int nsub, int S, int BS, int*
 // ---------------------------------------------------------------------------
 // advection right-hand side at block-local node t (tile coordinates i)
 // ---------------------------------------------------------------------------
-// (sw: the swirl tables' slices along the region, SWS entries apart; see load_swirl)
+// (sw: the swirl tables' slices along the region, S entries apart; see load_swirl)
 // VK: where the velocity comes from -- 0 by ph.kind at run time (the swirl from its
 // tables in HBM, or from the LDS slices sw where given), 1 the swirl from the LDS slices
 // sw, 2 the constant velocity.  Callers that know the kind pass 1 or 2, so that no
 // generic load (an LDS slice or an HBM table) is left in the stencil loop.
-template <int DIM, int BS, int S, int H, typename TT, int SWS = S, int VK = 0>
+template <int DIM, int BS, int S, int H, typename TT, int VK = 0>
 __device__ __forceinline__ TT rhs_adv(const TT* T, const int* i, const int* t, const BlockDesc& d, TT r,
                                       const Physics& ph, const LevelTab& lt, double cfac, const double* sw,
                                       const int* l) {
@@ -522,9 +522,9 @@ __device__ __forceinline__ TT rhs_adv(const TT* T, const int* i, const int* t, c
   double s2x, sx, s2y, sy;
   if (VK == 1 || sw) {
     s2x = sw[l[0]];
-    sx = sw[SWS + l[0]];
-    s2y = sw[2 * SWS + l[1]];
-    sy = sw[3 * SWS + l[1]];
+    sx = sw[S + l[0]];
+    s2y = sw[2 * S + l[1]];
+    sy = sw[3 * S + l[1]];
   } else {
     const int nl = lt.nl[d.level], shift = ph.jmax - d.level;
     int gx = d.c[0] * (BS - 1) + t[0];
@@ -783,8 +783,8 @@ __device__ __forceinline__ void stage_pass(const StageArgs& A, const StageVar& V
           // (one field in 2D: the swirl reads its LDS slices, any other kind is the
           // constant velocity)
           constexpr int VK0 = DIM == 2 && NF == 1 ? 2 : 0;
-          const TT kv = sw_lds ? rhs_adv<DIM, BS, S, HW, TT, S, 1>(tile, i, tq[e], d, r, A.ph, A.lt, V.cfac, swirl, l)
-                               : rhs_adv<DIM, BS, S, HW, TT, S, VK0>(tile, i, tq[e], d, r, A.ph, A.lt, V.cfac, nullptr, l);
+          const TT kv = sw_lds ? rhs_adv<DIM, BS, S, HW, TT, 1>(tile, i, tq[e], d, r, A.ph, A.lt, V.cfac, swirl, l)
+                               : rhs_adv<DIM, BS, S, HW, TT, VK0>(tile, i, tq[e], d, r, A.ph, A.lt, V.cfac, nullptr, l);
           if (V.stage < 4) {
             ((KT*)V.kout)[qa[e]] = (KT)kv;
           } else {
@@ -1800,9 +1800,18 @@ int stage_threads(const Shape& s, int precision, int nsub, int* tpb, int cap) {
   return n;
 }
 
-hipError_t launch_stage(const Shape& s, int precision, Variant v, int grid, int ncu, const StageArgs& a, hipStream_t st) {
+// workgroups of a kernel that loops over n blocks' sub-tiles
+static int loop_grid(const Shape& s, int n, int nsub, int max_grid) {
+  long items = n;
+  for (int a = 0; a < s.dim; ++a) items *= nsub;
+  return (int)std::min((long)max_grid, items);
+}
+
+hipError_t launch_stage(const Shape& s, int precision, Variant v, int max_grid, int ncu, const StageArgs& a,
+                        hipStream_t st) {
   if (v.nsub == 1 && v.tpb == zone_threads(s))
     return s.dim == 3 ? launch_stage3(precision, a, st) : launch_stage2(s, precision, ncu, a, st);
+  const int grid = loop_grid(s, a.topo.h.n_blocks, v.nsub, max_grid);
 #define X(D, B, W, F, P, NS, T)                                                                  \
   if (s.dim == D && s.bs == B && s.hw == W && s.nf == F && precision == P && v.nsub == NS &&     \
       v.tpb == T)                                                                                \
@@ -1969,9 +1978,10 @@ static hipError_t mr_go(int grid, const MrArgs& a, hipStream_t st) {
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_mr(const Shape& s, int nsub, int tpb, int grid, const MrArgs& a, hipStream_t st) {
+hipError_t launch_mr(const Shape& s, int nsub, int tpb, int max_grid, const MrArgs& a, hipStream_t st) {
   if (nsub == 1) return s.dim == 2 ? launch_mr2(s, tpb, a, st) : tpb == 256 ? launch_mr3(a, st) : hipErrorInvalidValue;
   if (tpb != 256) return hipErrorInvalidValue;
+  const int grid = loop_grid(s, a.topo.h.n_blocks, nsub, max_grid);
 #define X(D, B, W, F, NS) \
   if (s.dim == D && s.bs == B && s.hw == W && s.nf == F && nsub == NS) return mr_go<D, B, F, NS>(grid, a, st);
   MRB_AUX_VARIANTS(X)

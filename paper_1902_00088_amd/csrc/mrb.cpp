@@ -632,7 +632,7 @@ mrb_status build_descriptors(mrb_ctx* c) {
     const int lo = (int)((long)n * t / nt), hi = (int)((long)n * (t + 1) / nt);
     part[t].clear();
     part[t].reserve((size_t)(hi - lo) * (d == 2 ? 13 : 57));
-    for (int i = lo; i < hi && !err[t]; ++i) 
+    for (int i = lo; i < hi && !err[t]; ++i)
       err[t] = d == 2 ? block_entries<2>(c, i, part[t], hblk[i]) : block_entries<3>(c, i, part[t], hblk[i]);
   };
   {
@@ -956,7 +956,7 @@ int pick_mr(const mrb_ctx* c) {
 }
 
 // launch one RK stage (fused) or ghost + RHS per level (plain)
-mrb_status run_stage(mrb_ctx* c, int s, const StageArgs& a0, bool fixed_grid = false, bool time_it = true) {
+mrb_status run_stage(mrb_ctx* c, int s, const StageArgs& a0, bool time_it = true) {
   StageArgs a = a0;
   const int n = (int)nblk(c);
   if (c->cfg.form == MRB_FORM_PLAIN) {
@@ -971,13 +971,9 @@ mrb_status run_stage(mrb_ctx* c, int s, const StageArgs& a0, bool fixed_grid = f
     return MRB_OK;
   }
   const Variant v = pick_stage(c);
-  long work = n;
-  for (int d = 0; d < c->cfg.dim; ++d) work *= v.nsub;
   c->stage_ran = stage_form(c, v, n);
   TimeScope ts(c, T_STAGE, (double)n * c->bsz * stage_bytes(c, s), 1, time_it);
-  HIPCHK(c, launch_stage(c->shape, c->cfg.precision, v,
-                         fixed_grid ? c->grid : grid_for(c, work), c->ncu, a,
-                         c->stream));
+  HIPCHK(c, launch_stage(c->shape, c->cfg.precision, v, c->grid, c->ncu, a, c->stream));
   return MRB_OK;
 }
 
@@ -1088,21 +1084,21 @@ void rk4t_analysis_args(mrb_ctx* c, Rk4tArgs& ra, const int* smap) {
 }
 
 // the four stages of one RK4 step; results go to k1..k3 and u_new (u is read only).
-// fixed_grid (graph capture) always takes the four-launch path.
-mrb_status sweep(mrb_ctx* c, double t, double dt, bool fixed_grid = false) {
+// captured (in a graph): always the four launches.
+mrb_status sweep(mrb_ctx* c, double t, double dt, bool captured = false) {
   const double h2 = dt * 0.5, h6 = dt / 6.0;
   const double ts[4] = {t, t + h2, t + h2, t + dt};
   StageArgs a = stage_args(c);
   a.h6 = h6;
   const double alpha[4] = {0.0, h2, h2, dt};
-  const int tn = fixed_grid ? 0 : rk4t_pick(c);
+  const int tn = captured ? 0 : rk4t_pick(c);
   if (tn > 0) return launch_tiled(c, tn, rk4t_args(c, t, dt), false);
   // fused form: one event pair around the four stage launches
   const bool fused = c->cfg.form == MRB_FORM_FUSED;
   double sweep_bytes = 0.0;
   for (int s = 1; s <= 4; ++s) sweep_bytes += (double)nblk(c) * c->bsz * stage_bytes(c, s);
   TimeScope sweep_scope(c, T_STAGE, sweep_bytes, 4, fused);
-  if (!fixed_grid && sweep_in_one(c)) {
+  if (!captured && sweep_in_one(c)) {
     SweepArgs sa;
     std::memset(&sa, 0, sizeof sa);
     sa.a = a;
@@ -1128,7 +1124,7 @@ mrb_status sweep(mrb_ctx* c, double t, double dt, bool fixed_grid = false) {
     a.kout = s < 4 ? c->k[s - 1] : nullptr;
     a.cfac = 1.0;
     if (c->cfg.physics == MRB_ADV_SWIRL && c->cfg.phys[0] > 0.0) a.cfac = std::cos(M_PI * ts[s - 1] / c->cfg.phys[0]);
-    mrb_status r = run_stage(c, s, a, fixed_grid, !fused);
+    mrb_status r = run_stage(c, s, a, !fused);
     if (r) return r;
   }
   return MRB_OK;
@@ -1340,15 +1336,13 @@ MrArgs mr_args(mrb_ctx* c) {
 }
 
 // `spec`: a memoised coarsening of the current grid whose mothers the pass also writes
-mrb_status launch_mr_kernel(mrb_ctx* c, bool fixed_grid, const mrb_ctx::Memo* spec = nullptr) {
+mrb_status launch_mr_kernel(mrb_ctx* c, const mrb_ctx::Memo* spec = nullptr) {
   const int n = (int)nblk(c);
   MrArgs a = mr_args(c);
   if (spec) a.smap = spec->smap;
   const int ns = pick_mr(c);
-  long work = n;
-  for (int q = 0; q < c->cfg.dim; ++q) work *= ns;
   TimeScope ts(c, T_MR, (double)n * c->bsz * 8.0);
-  HIPCHK(c, launch_mr(c->shape, ns, mr_tpb(c, ns), fixed_grid ? c->grid : grid_for(c, work), a, c->stream));
+  HIPCHK(c, launch_mr(c->shape, ns, mr_tpb(c, ns), c->grid, a, c->stream));
   return MRB_OK;
 }
 
@@ -1382,7 +1376,7 @@ mrb_status mr_readback(mrb_ctx* c) {
 }
 
 mrb_status do_mr_pass(mrb_ctx* c) {
-  mrb_status r = launch_mr_kernel(c, false);
+  mrb_status r = launch_mr_kernel(c);
   if (r) return r;
   return mr_readback(c);
 }
@@ -1748,7 +1742,7 @@ mrb_status do_adapt(mrb_ctx* c, int* npass, bool first_launched, bool first_fuse
   mrb_ctx::Memo* e = spec_entry(c);
   // a first pass launched here also writes the speculated mothers
   const bool fused = e && e->smap && (first_launched ? first_fused : true);
-  if (!first_launched && (s = launch_mr_kernel(c, false, fused ? e : nullptr))) return s;
+  if (!first_launched && (s = launch_mr_kernel(c, fused ? e : nullptr))) return s;
   if (!e) {
     if ((s = wait_stream(c))) return s;
     if (first_tiled) ana_combine(c);
@@ -1770,7 +1764,7 @@ mrb_status do_adapt(mrb_ctx* c, int* npass, bool first_launched, bool first_fuse
   if ((s = spec_begin(c, e, fused, sn))) return s;
   if (!second_folded) {
     c->flag_set = 1;
-    s = launch_mr_kernel(c, false);
+    s = launch_mr_kernel(c);
     c->flag_set = 0;
     if (s) return s;
   }
@@ -2008,7 +2002,7 @@ mrb_status step_graph(mrb_ctx* c, double t, double dt) {
     double* u0 = c->u;
     if (!e) {
       std::swap(c->u, c->unew);
-      e = launch_mr_kernel(c, true, smap ? se : nullptr);
+      e = launch_mr_kernel(c, smap ? se : nullptr);
       std::swap(c->u, c->unew);
     }
     hipGraph_t graph = nullptr;
@@ -2375,10 +2369,8 @@ mrb_status dev_adapt(mrb_ctx* c, int* npass) {
       m.flags = D.flags;
       m.maxd = D.maxd;
       const int ns = pick_mr(c);
-      long work = n;
-      for (int q = 0; q < c->cfg.dim; ++q) work *= ns;
       TimeScope ts(c, T_MR, (double)n * c->bsz * 8.0);
-      HIPCHK(c, launch_mr(c->shape, ns, mr_tpb(c, ns), grid_for(c, work), m, c->stream));
+      HIPCHK(c, launch_mr(c->shape, ns, mr_tpb(c, ns), c->grid, m, c->stream));
     }
     ++passes;
     c->n_mr++;
@@ -2769,9 +2761,7 @@ mrb_status mrb_mr_pass_noalloc(mrb_ctx* c, int8_t* flags, double* maxd) {
   MrArgs a = mr_args(c);
   a.acc = (unsigned long long*)base;
   a.done = (int*)(base + acc_bytes);
-  long work = (long)n;
-  for (int q = 0; q < c->cfg.dim; ++q) work *= ns;
-  HIPCHK(c, launch_mr(c->shape, ns, 256, grid_for(c, work), a, c->stream));
+  HIPCHK(c, launch_mr(c->shape, ns, 256, c->grid, a, c->stream));
   mrb_status r = mr_readback(c);
   c->dev.have_flags = false;   // the newest analysis is the host's copy
   if (flags) std::memcpy(flags, c->last_flags.data(), c->last_flags.size());
@@ -3198,7 +3188,7 @@ mrb_status mrb_tune(mrb_ctx* c, int nsub, int reps, double dt, int* chosen) {
                 } else {
                   r = launch_tiled(c, c->rk4t_nsub, ra, false);
                   c->flag_set = 0;
-                  if (!r) r = launch_mr_kernel(c, false);
+                  if (!r) r = launch_mr_kernel(c);
                 }
               }
               float ms = 0.f;
@@ -3362,10 +3352,7 @@ mrb_status mrb_tune(mrb_ctx* c, int nsub, int reps, double dt, int* chosen) {
     }
     mrb_status tr = time_variants("mr", &c->nsub_mr, na, [&](int v, int k) -> mrb_status {
       MrArgs a = mr_args(c);
-      const int n = (int)c->hblk.size();
-      long work = n;
-      for (int q = 0; q < c->cfg.dim; ++q) work *= v;
-      for (int j = 0; j < k; ++j) HIPCHK(c, launch_mr(c->shape, v, 256, grid_for(c, work), a, c->stream));
+      for (int j = 0; j < k; ++j) HIPCHK(c, launch_mr(c->shape, v, 256, c->grid, a, c->stream));
       return MRB_OK;
     });
     if (tr) return done(tr);
@@ -3377,12 +3364,11 @@ mrb_status mrb_tune(mrb_ctx* c, int nsub, int reps, double dt, int* chosen) {
       if (nt > 1) {
         float best[4] = {1e30f, 1e30f, 1e30f, 1e30f};
         MrArgs a = mr_args(c);
-        const long work = (long)c->hblk.size();
         for (int round = 0; round < kRounds; ++round)
           for (int i = 0; i < nt; ++i) {
-            HIPCHK(c, launch_mr(c->shape, 1, tp[i], grid_for(c, work), a, c->stream));   // warm-up
+            HIPCHK(c, launch_mr(c->shape, 1, tp[i], c->grid, a, c->stream));   // warm-up
             HIPCHK(c, hipEventRecord(e0, c->stream));
-            for (int j = 0; j < reps; ++j) HIPCHK(c, launch_mr(c->shape, 1, tp[i], grid_for(c, work), a, c->stream));
+            for (int j = 0; j < reps; ++j) HIPCHK(c, launch_mr(c->shape, 1, tp[i], c->grid, a, c->stream));
             float ms = 0.f;
             if (hipEventRecord(e1, c->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
                 hipEventElapsedTime(&ms, e0, e1) != hipSuccess)
