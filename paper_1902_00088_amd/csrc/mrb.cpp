@@ -617,9 +617,11 @@ mrb_status build_descriptors(mrb_ctx* c) {
   const int n = (int)c->leaves.size();
   std::vector<BlockDesc> hblk(n);
   int nt = 1;
-  // A block takes 30 ns in 2D and 130 in 3D; waking the workers and waiting for them about 100 us.
-  // 4,096 blocks of 2D: 120 us alone, 115 to 370 with 4 to 16 threads; of 3D 547: 59 alone, 49
-  // with 8, and 1,793: 230 alone, 105 with 16.
+  // A block takes 30 to 40 ns in 2D and 110 to 130 in 3D; waking the workers, waiting for them and
+  // joining their lists costs 2D grids more than they share until there are 16 of them: 4,096
+  // blocks 128 us alone, 151 with 16 threads; 16,384 537 and 531; 40,960 (two levels) 1,595 and
+  // 1,392; 65,536 2,129 and 2,188; 163,840 6,816 and 6,129.  3D, with n / 64 threads up to 16: 288
+  // blocks 36 alone, 42; 512 55 and 61; 2,304 286 and 167; 18,432 2,287 and 1,130.
   if (n >= (d == 2 ? 16384 : (int)c->desc_thread_min)) {
     const int hc = (int)std::max(1u, std::thread::hardware_concurrency());
     nt = std::max(1, std::min({16, hc, n / (d == 2 ? 1024 : 64)}));
