@@ -95,8 +95,9 @@ __device__ __forceinline__ T plane_value(const T* c, int k) {
 // ---------------------------------------------------------------------------
 // RK stage of whole blocks.  448 threads: one of the 21 x 21 columns of block + halo
 // each (columns outside the block along both x and y feed the predictions only).  The
-// tile kernel it replaces spent 21,000 wave instructions a block, half of them on owners
-// resolved point by point; this one spends 6,900.  What bounds it now is memory: lines of
+// tile kernel it replaces spent 21,000 vector instructions of a wave on a block, half of them
+// on owners resolved point by point; this one spends 7,000 (40% of a compute unit's cycles;
+// LDS 23%).  What bounds it now is memory: lines of
 // 128 bytes for x-halo segments of two points, and the rounds of latency of a workgroup
 // (14 to 18 us, two per compute unit; three are no faster, since their blocks outgrow the
 // XCD's L2).  1,793 blocks on three levels: 55 us a stage mixed and 83 us FP64 on average,
@@ -473,7 +474,8 @@ __global__ void __launch_bounds__(MT, 3) k_mr3(MrArgs A) {
 // thread interpolates one of the child's 17 x 17 columns.  Nodes on the parent's boundary
 // that a finer leaf holds are copied in a pass of their own, all loads in flight, so no
 // column waits for them.  428 parents to 3,424 children: 66 us (its stores, 135 MB) against
-// 111 us.
+// 111 us for sub-tiles of children; 8 and 29 parents, a whole call: 19 and 26 us against 24
+// and 48.
 // ---------------------------------------------------------------------------
 constexpr int LW = 9;                   // coarse lattice of a parent beside coarser leaves
 

@@ -133,7 +133,6 @@ struct SweepArgs {
 // are all on one level): u over the region plus 4 halo widths, every stage in LDS.
 struct Rk4tArgs {
   Topo topo;
-  int b0, nb;             // blocks of this launch (set by launch_rk4t)
   const double* u;
   double* unew;
   double alpha[4];        // y_s = u + alpha_s k_{s-1}
@@ -264,8 +263,8 @@ inline ZoneForm zone_form(const Shape& s, int precision, int n, int ncu) {
 inline int mr_workgroup(const Shape& s, int asked) { return s.bs == 17 ? 320 : asked; }
 hipError_t launch_plain(const Shape& s, int grid, const StageArgs& a, hipStream_t st);  // ghost + RHS kernels
 // overlapped-tile RK4 step; hipErrorInvalidValue if the shape has no such kernel
-// (threads per workgroup: 256; with the analysis on whole blocks also 512 or 1024;
-// refine: the refinement of the parents (every one, a forest on one level) folded in,
+// (tpb: 256; with the analysis on whole blocks and quarters also 512 or 1024, the threads of
+// a workgroup; refine: the refinement of the parents (every one, a forest on one level) folded in,
 // with the analysis only; mothers: the second analysis of a speculated coarsening that
 // merges every block, with refine only)
 hipError_t launch_rk4t(const Shape& s, int precision, int nsub, bool analysis, bool refine, bool mothers, int tpb,

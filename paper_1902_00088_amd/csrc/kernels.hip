@@ -1,7 +1,7 @@
 // HIP kernels of the block-multiresolution sweep (gfx950): sub-tiled stages and analysis, the
 // one-launch sweep, the overlapped-tile RK4 step, the plain form, coarsening and read-back.
 // Whole blocks' stages, analysis, refinement and filter are in column3.hip (3D) and plane2.hip
-// (2D), which the dispatch at the end prefers.
+// (2D); which stage runs is decided in mrb.cpp (pick_stage).
 //
 // A workgroup of a stage handles one block (or one sub-tile of a block) per iteration of a
 // loop over a work list.
@@ -880,10 +880,10 @@ __global__ void __launch_bounds__(256) k_sweep(SweepArgs S) {
 // velocity products in registers, so LDS holds two stage-value arrays only (38 KB in FP64
 // for a whole block, 84 KB with u and the slopes in LDS) and a point reads its eight
 // neighbours and nothing else per stage.  Vector issue and LDS reads bound large forests
-// (60% each): 4,096 whole blocks of 33^2 in FP64 take 56 us with 512 threads against 217 us
-// with everything in LDS and 256.  Threads that own vertical strips instead read less LDS
-// but computed more of the halo (63 us).  Small forests are bound by the launch's chain of
-// latencies: the 64-block folded step takes 9.9 us against 11.8.
+// (three quarters of the cycles each): 4,096 whole blocks of 33^2 in FP64 take 56 us with 512
+// threads against 217 us with everything in LDS and 256.  Threads that own vertical strips
+// instead read less LDS but computed more of the halo (63 us).  Small forests are bound by the
+// launch's chain of latencies: the 64-block folded step takes 9.9 us against 11.8.
 // ---------------------------------------------------------------------------
 // NaN-propagating maxima of two values over a workgroup of TPB threads (values as for
 // wave_nanmax): wave maxima through red (2 TPB / 64 doubles of LDS; a barrier must lie
@@ -1018,11 +1018,12 @@ __global__ void __launch_bounds__(TPB, TPB >= 512 ? 4 : 2) k_rk4t(Rk4tArgs A) {
   __shared__ int tab[9];                            // same-level holder by direction
   __shared__ double sw[4 * TW];
   __shared__ double red[2 * (TPB / 64)];
+  const int nblk = A.topo.h.n_blocks;
   const BlockDesc* blk = A.topo.blk();
   const int tid = threadIdx.x;
-  const XcdWork it(A.nb * NSUBT);   // one work item per workgroup
+  const XcdWork it(nblk * NSUBT);   // one work item per workgroup
   if (!it.ok()) return;
-  const int b = A.b0 + it.w / NSUBT;
+  const int b = it.w / NSUBT;
   // everything the work item's addresses depend on, requested at once: the block, its
   // (or, with REF, its parent's) entry row up to the row stride -- entries past the
   // count are ignored --, the speculation map and the refinement plan's child slot
@@ -1866,7 +1867,7 @@ static hipError_t rk4t_go(bool ana, bool ref, bool ma, int tpb, int grid, const 
 
 static hipError_t rk4t_launch(const Shape& s, int precision, int nsub, bool analysis, bool refine, bool mothers, int tpb,
                               const Rk4tArgs& a, hipStream_t st) {
-  const int grid = a.nb * nsub * nsub;   // one workgroup per work item
+  const int grid = a.topo.h.n_blocks * nsub * nsub;   // one workgroup per work item
 #define X(B, P, NS)                                                                                              \
   if (s.bs == B && precision == P && nsub == NS) {                                                              \
     if constexpr (P == 0) return rk4t_go<B, NS, double, double>(analysis, refine, mothers, tpb, grid, a, st);   \
@@ -1881,12 +1882,28 @@ hipError_t launch_rk4t(const Shape& s, int precision, int nsub, bool analysis, b
                        const Rk4tArgs& args, hipStream_t st) {
   if (s.dim != 2 || s.hw != 2 || s.nf != 1) return hipErrorInvalidValue;
   // A launch holds fewer than 2^32 threads: 2^20 workgroups of up to 1,024.  Forests of more
-  // (4 x 4 sub-tiles of 65,536 blocks on) take several launches, each over a range of blocks.
-  const int n = args.topo.h.n_blocks, most = (1 << 20) / (nsub * nsub);
-  Rk4tArgs a = args;
+  // (4 x 4 sub-tiles of more than 65,536 blocks) take several launches, each over a range of
+  // blocks: whole families (the range starts at a multiple of 4), and everything a block or its
+  // parent indexes starts at the range's first.  (The range's start as an argument of the kernel
+  // cost the 64-block step 0.2 us.)
+  const int n = args.topo.h.n_blocks, parts = nsub * nsub, most = (1 << 20) / parts;
   hipError_t e = hipSuccess;
-  for (a.b0 = 0; a.b0 < n && e == hipSuccess; a.b0 += a.nb) {
-    a.nb = std::min(most, n - a.b0);
+  for (int b0 = 0; b0 < n && e == hipSuccess; b0 += most) {
+    Rk4tArgs a = args;
+    TopoHeader& h = a.topo.h;
+    h.n_blocks = std::min(most, n - b0);
+    h.off_blk += b0 * (int)sizeof(BlockDesc);
+    h.off_nb += b0 * h.nb_stride * (int)sizeof(NbEntry);
+    if (refine) {
+      h.off_pblk += b0 / 4 * (int)sizeof(BlockDesc);
+      h.off_pnb += b0 / 4 * h.pnb_stride * (int)sizeof(NbEntry);
+      h.off_ref += b0 / 4 * (int)sizeof(RefineDesc);
+    }
+    if (a.flags) a.flags += b0;
+    if (a.maxd) a.maxd += b0;
+    if (a.smap) a.smap += b0;
+    if (a.part) a.part += (size_t)b0 * parts;
+    if (a.mq) a.mq += (size_t)b0 * parts;
     e = rk4t_launch(s, precision, nsub, analysis, refine, mothers, tpb, a, st);
   }
   return e;

@@ -293,9 +293,10 @@ __global__ void __launch_bounds__(TPB) k_stage2(StageArgs A) {
 // (see ns_fluxes in kernels.hip, whose operations these are, point by point).  p / rho is
 // formed once per tile point (it had cost eight FP64 divisions per flux point), and a
 // node's gradients, stresses and momentum factors pass from its fluxes to its right-hand
-// side in registers.  Bound by vector instructions (4,800 a half block, half of their
-// issue slots), LDS reads (40 us) and memory (260 MB, 50 us) together, overlapped by the two
-// to four workgroups that fit a compute unit's LDS.  2,944 blocks on five levels: 89 us a stage
+// side in registers.  Thirds, mixed, are bound by vector instructions (3,800 of a wave a third,
+// 70% of a compute unit's cycles), LDS (52%, a quarter of it bank conflicts) and memory (260 MB,
+// 50 us) together, overlapped by the two to four workgroups that fit a compute unit's LDS; FP64
+// issues half of the time and waits for LDS as long.  2,944 blocks on five levels: 89 us a stage
 // mixed against 244 us for whole blocks of 256 threads; 1,024 blocks FP64: 42 against 76 us.
 // ---------------------------------------------------------------------------
 constexpr int NB = 33;
@@ -476,7 +477,8 @@ __global__ void __launch_bounds__(T) k_stage_ns(StageArgs A) {
 // ---------------------------------------------------------------------------
 // Shock-capturing filter after a time step (formulas at FilterArgs), half or a third of a
 // block per workgroup: per axis the pressure sensor of one point more than the region on either
-// side, then the switched second-order fluxes.  2,944 blocks: 69 us (205 MB of block data,
+// side, then the switched second-order fluxes.  Vector instructions fill 64% of a compute
+// unit's cycles (two divisions a sensor), LDS 39%.  2,944 blocks: 68 us (205 MB of block data,
 // 3.0 TB/s) against 149 us for whole blocks of 256 threads, one per compute unit.
 // ---------------------------------------------------------------------------
 constexpr int FHW = 3;   // p is read up to 3 beyond the region, the other fields 1
@@ -591,9 +593,10 @@ __device__ __forceinline__ double half_value(const double* ev, const double* od,
 // Analysis of a whole block per workgroup (operations and stores as k_mr in kernels.hip):
 // a thread owns a few of the block's points, LDS holds only the even points and their odd
 // neighbours along x (6 KB a field, so that eight blocks of one field share a compute unit).
-// Bound by memory on large grids (4,096 blocks, 36 MB: 15.6 us against 39.7 for a tile in
-// LDS) and by its chain of loads on small ones (740 to 2,900 blocks: 7.4 against 12.9 us; four
-// fields, 740 to 2,900 blocks on five levels: 21.6 against 40.4 us).
+// Bound by vector instructions on large grids (80% of a compute unit's cycles; 4,096 blocks,
+// 36 MB: 15.6 us against 39.7 for a tile in LDS) and by its chain of loads on small ones (740
+// to 2,900 blocks: 7.4 against 12.9 us; four fields, 740 to 2,900 blocks on five levels: 21.6
+// against 40.4 us).
 // ---------------------------------------------------------------------------
 template <int BS, int NF, int TPB>
 __global__ void __launch_bounds__(TPB) k_mr2(MrArgs A) {
@@ -880,8 +883,8 @@ hipError_t launch_refine2(const Shape& s, const RefineArgs& a, hipStream_t st) {
   return go2(k_refine2<17, 1, 320>, n, 0, 320, st, a);
 }
 
-// (halves and thirds as in the stage: 2,944 blocks 70.2 us in halves, 68.7 in thirds; 1,024:
-// 25.9 and 24.7)
+// (halves and thirds as in the stage: thirds are 2% faster on 2,944 blocks, 68 us, and 5% on
+// 1,024, 25 us)
 hipError_t launch_filter(int ncu, const FilterArgs& a, hipStream_t st) {
   const int n = a.topo.h.n_blocks;
   if (n > ncu) return go2(k_filter2<11, 448>, ns_parts(11) * n, FilterLds<11, 448>::bytes, 448, st, a);
