@@ -95,6 +95,9 @@ def solver(cfg, levels, coords):
 
 
 def run(tmp_path, code):
+    import paper_1902_00088_amd as M
+    if not os.path.exists(M.LIB_PATH):
+        M.build()
     so = os.path.join(str(tmp_path), "libamdhip64.so.7")
     vers = os.path.join(str(tmp_path), "versions")
     with open(vers, "w") as f:
