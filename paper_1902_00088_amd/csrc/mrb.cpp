@@ -618,9 +618,9 @@ mrb_status build_descriptors(mrb_ctx* c) {
   std::vector<BlockDesc> hblk(n);
   int nt = 1;
   // A block takes 30 to 40 ns in 2D and 110 to 130 in 3D; waking the workers, waiting for them and
-  // joining their lists costs 2D grids more than they share until there are 16 of them: 4,096
-  // blocks 128 us alone, 151 with 16 threads; 16,384 537 and 531; 40,960 (two levels) 1,595 and
-  // 1,392; 65,536 2,129 and 2,188; 163,840 6,816 and 6,129.  3D, with n / 64 threads up to 16: 288
+  // joining their lists takes 2D grids about what 16 of them share: 4,096 blocks 128 us alone, 151
+  // with 16 threads; 10,240 (two levels) 401 and 380; 16,384 537 and 531; 40,960 (two levels) 1,595
+  // and 1,392; 65,536 2,129 and 2,188; 163,840 6,816 and 6,129.  3D, with n / 64 threads up to 16: 288
   // blocks 36 alone, 42; 512 55 and 61; 2,304 286 and 167; 18,432 2,287 and 1,130.
   if (n >= (d == 2 ? 16384 : (int)c->desc_thread_min)) {
     const int hc = (int)std::max(1u, std::thread::hardware_concurrency());
@@ -3070,7 +3070,7 @@ mrb_status mrb_tune(mrb_ctx* c, int nsub, int reps, double dt, int* chosen) {
       }
     size_t bi = 0;
     for (size_t i = 0; i < cand.size(); ++i) {
-        // keys: sub-tiles per axis, "t<threads>" unless 256, "p<workgroups per block>" of a
+      // keys: sub-tiles per axis, "t<threads>" unless 256, "p<workgroups per block>" of a
       // zone-owner kernel unless one, "L" for the level-sorted order
       char buf[64], tp[32] = "";
       const ZoneForm f = stage_form(c, Variant{cand[i].nsub, cand[i].tpb}, (int)nblk(c));
